@@ -13,6 +13,7 @@
 
 #include "pks_internal.h"
 #include "plan.h"
+#include "steady.hpp"
 
 namespace pks {
 
@@ -210,8 +211,33 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
     TileConfig cfg = forced ? *forced : tuned_config(model.nx, model.ny, B, total, prec);
     if (cfg.ept < kMinEpt) cfg.ept = kMinEpt;
     if (!small_supported(model.nx)) cfg.ept1 = 0;   // the large-state path reads only cfg.blocks
-    hipError_t e = launch_precompute(model.nx, model.ny, nmodels, model, ws, L, mixed, passes,
-                                     (passes & 1) != 0, s, tv, tv ? offsets : nullptr, B);
+    // Time-invariant models with settling covariances: the setup decides on the
+    // device; the general kernels follow and return at once when it has done
+    // the work.
+    hipError_t e;
+    const int* skip = nullptr;
+    if ((passes & 1) && !tv && !model.per_sequence && steady::applies(model.nx, model.ny, B, total, mixed)) {
+        char* base = static_cast<char*>(ws);
+        steady::Args t{};
+        t.nx = model.nx; t.ny = model.ny; t.B = B;
+        t.total = total;
+        t.offsets = offsets;
+        t.smooth = (passes & 2) != 0;
+        t.reset = 1;
+        t.F = model.F; t.u = model.u; t.Q = model.Q; t.H = model.H; t.d = model.d; t.R = model.R;
+        t.m0 = model.m0; t.P0 = model.P0;
+        t.y = y; t.m = m; t.P = P; t.ms = ms; t.Ps = Ps;
+        t.status = reinterpret_cast<int*>(base + L.status);
+        t.ctl = t.status + kSteadyCtl;
+        const size_t r0 = small ? L.thr : L.large, r1 = small ? L.top_agg : L.ll_step;
+        if (steady::layout(t, base + r0, r1 - r0)) {
+            e = steady::launch(t, mixed, s);
+            if (e != hipSuccess) return hip_fail(e, "settled-covariance kernels");
+            skip = t.ctl;
+        }
+    }
+    e = launch_precompute(model.nx, model.ny, nmodels, model, ws, L, mixed, passes, (passes & 1) != 0, s, tv,
+                          tv ? offsets : nullptr, B, skip);
     if (e != hipSuccess) return hip_fail(e, "precompute kernel");
     // a single time-varying sequence runs as one packed sequence (offsets {0, T},
     // written by the precompute's preparation kernel) through the per-step-constant
@@ -223,6 +249,7 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
     a.P = P;
     a.ms = ms;
     a.Ps = Ps;
+    a.skip = skip;
     if (!small) {
         void* region = static_cast<char*>(ws) + L.large;
         if (passes & 1) {

@@ -64,6 +64,7 @@ constexpr int kTopAggWords = 6 * 16;
 
 constexpr int kStatusOk = 0x7fffffff;     // "no failure" value of the numeric flag
 constexpr int kStatusMagic = 0x504b5331;  // marks a prepared status word
+constexpr int kSteadyCtl = 16;            // word of the status block where the settled-covariance flags start
 
 // ---------------------------------------------------------------------------
 // Workspace layout (byte offsets from ws), computed on the host.
@@ -127,7 +128,18 @@ struct ScanArgs {
     int* status;
     const int* model_fail;       // [nmodels] 1 = the model's precompute failed
     int nmodels;
+    const int* skip;             // nonzero *skip: another path has done the work, return at once (nullptr: none)
 };
+
+// The work of a launch is already done (ScanArgs::skip; the same for every
+// thread).  The empty asm statement asks for one argument of each 64-byte line
+// of the argument block along with `skip`: the lines then arrive together,
+// where the rest would otherwise be fetched only after the branch (0.3 us a
+// launch).
+__device__ __forceinline__ bool skipped(const ScanArgs& a) {
+    asm volatile("" ::"s"(a.total), "s"(a.P), "s"(a.nthr));
+    return a.skip && *a.skip != 0;
+}
 
 // Offset (in words) of the constants of step k of sequence b: one block per
 // model (one per sequence), or one block per step for a time-varying model.
@@ -164,7 +176,8 @@ bool small_supported(int nx);
 // and a failing factorisation flags its sequence directly.
 hipError_t launch_precompute(int nx, int ny, int32_t nmodels, const pks_model& model,
                              void* ws, const WsLayout& L, bool mixed, int what, bool reset, hipStream_t s,
-                             bool tv = false, const int64_t* tv_offsets = nullptr, int32_t B = 1);
+                             bool tv = false, const int64_t* tv_offsets = nullptr, int32_t B = 1,
+                             const int* skip = nullptr);
 // passes: 1 = filter, 2 = smoother, 3 = both (fused where possible)
 hipError_t launch_small(ScanArgs a, bool mixed, int passes, hipStream_t s);
 TileConfig small_default_config(int nx, int64_t total, bool mixed);
@@ -228,6 +241,6 @@ bool launch_ll_w16(int nx, int ny, int64_t total, const double* m0, const double
 // one wavefront per model (what: 1, 2 or 3 as for launch_precompute); false:
 // not applicable, nothing launched
 bool launch_w16_precompute(int nx, int ny, int32_t nmodels, const pks_model& model, double* consts64, float* consts32,
-                           int* status, int* model_fail, int what, bool reset, hipStream_t s);
+                           int* status, int* model_fail, int what, bool reset, hipStream_t s, const int* skip = nullptr);
 
 }  // namespace pks

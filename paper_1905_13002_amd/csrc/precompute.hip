@@ -43,6 +43,7 @@ struct PrecomputeArgs {
     int tv;       // time-varying model: one row of F, u, Q, H, d, R per step, model index = step
     const int64_t* offsets;   // time-varying, batched: [B+1] packed sequences (else nullptr)
     int B;
+    const int* skip;      // as ScanArgs::skip
 };
 
 // Sequence holding step k of packed sequences (offsets[lo] <= k < offsets[lo + 1]).
@@ -199,6 +200,8 @@ __device__ void btranspose(double* dst, const double* src, int rows, int cols) {
 }
 
 __global__ __launch_bounds__(kThreads) void k_precompute(PrecomputeArgs a) {
+    asm volatile("" ::"s"(a.F), "s"(a.P0), "s"(a.status));       // (as in skipped())
+    if (a.skip && *a.skip != 0) return;
     extern __shared__ double lds[];
     const int b = blockIdx.x;
     if (b == 0 && threadIdx.x == 0 && !a.tv) {
@@ -462,8 +465,12 @@ struct WaveWriter {
     }
 };
 
-template <int NX, int NY>
+// GATED: returns at once when *a.skip is set (an instantiation of its own: the
+// test costs 0.35 us of the 8 us kernel)
+template <int NX, int NY, bool GATED>
 __global__ __launch_bounds__(64) void k_precompute_small(PrecomputeArgs a, int nmodels) {
+    if constexpr (GATED)
+        if (*a.skip != 0) return;
     using SP = SmallPre<NX, NY>;
     // Two independent chains per model, in different waves so that they run
     // concurrently: even blocks derive the shared constants of the steps k > 1,
@@ -644,34 +651,40 @@ __global__ __launch_bounds__(64) void k_precompute_small(PrecomputeArgs a, int n
     }
 }
 
-template <int NX>
+template <int NX, bool GATED>
 bool launch_small_pre_ny(int ny, PrecomputeArgs a, int nmodels, hipStream_t s) {
     const dim3 grid(2 * ((nmodels + 63) / 64)), block(64);    // even / odd blocks: the two halves
     switch (ny) {
-        case 1: hipLaunchKernelGGL((k_precompute_small<NX, 1>), grid, block, 0, s, a, nmodels); return true;
-        case 2: hipLaunchKernelGGL((k_precompute_small<NX, 2>), grid, block, 0, s, a, nmodels); return true;
-        case 3: hipLaunchKernelGGL((k_precompute_small<NX, 3>), grid, block, 0, s, a, nmodels); return true;
-        case 4: hipLaunchKernelGGL((k_precompute_small<NX, 4>), grid, block, 0, s, a, nmodels); return true;
+        case 1: hipLaunchKernelGGL((k_precompute_small<NX, 1, GATED>), grid, block, 0, s, a, nmodels); return true;
+        case 2: hipLaunchKernelGGL((k_precompute_small<NX, 2, GATED>), grid, block, 0, s, a, nmodels); return true;
+        case 3: hipLaunchKernelGGL((k_precompute_small<NX, 3, GATED>), grid, block, 0, s, a, nmodels); return true;
+        case 4: hipLaunchKernelGGL((k_precompute_small<NX, 4, GATED>), grid, block, 0, s, a, nmodels); return true;
+        default: return false;
+    }
+}
+
+template <bool GATED>
+bool launch_small_pre_nx(int nx, int ny, PrecomputeArgs a, int nmodels, hipStream_t s) {
+    switch (nx) {
+        case 1: return launch_small_pre_ny<1, GATED>(ny, a, nmodels, s);
+        case 2: return launch_small_pre_ny<2, GATED>(ny, a, nmodels, s);
+        case 3: return launch_small_pre_ny<3, GATED>(ny, a, nmodels, s);
+        case 4: return launch_small_pre_ny<4, GATED>(ny, a, nmodels, s);
         default: return false;
     }
 }
 
 bool launch_small_pre(int nx, int ny, PrecomputeArgs a, int nmodels, hipStream_t s) {
-    switch (nx) {
-        case 1: return launch_small_pre_ny<1>(ny, a, nmodels, s);
-        case 2: return launch_small_pre_ny<2>(ny, a, nmodels, s);
-        case 3: return launch_small_pre_ny<3>(ny, a, nmodels, s);
-        case 4: return launch_small_pre_ny<4>(ny, a, nmodels, s);
-        default: return false;
-    }
+    return a.skip ? launch_small_pre_nx<true>(nx, ny, a, nmodels, s) : launch_small_pre_nx<false>(nx, ny, a, nmodels, s);
 }
 
 }  // namespace
 
 hipError_t launch_precompute(int nx, int ny, int32_t nmodels, const pks_model& model, void* ws,
                              const WsLayout& L, bool mixed, int what, bool reset, hipStream_t s, bool tv,
-                             const int64_t* tv_offsets, int32_t B) {
+                             const int64_t* tv_offsets, int32_t B, const int* skip) {
     PrecomputeArgs a;
+    a.skip = skip;
     a.nx = nx;
     a.ny = ny;
     a.per_sequence = model.per_sequence ? 1 : 0;
@@ -705,7 +718,7 @@ hipError_t launch_precompute(int nx, int ny, int32_t nmodels, const pks_model& m
     if (!tv && a.what >= 1 && a.what <= 4 && w16_applies(nx, ny, true)) {
         prof_begin("k_w16_precompute", s);
         launch_w16_precompute(nx, ny, nmodels, model, a.consts64, a.mixed ? a.consts32 : nullptr, a.status,
-                              a.model_fail, a.what == 4 ? 1 : a.what, reset, s);
+                              a.model_fail, a.what == 4 ? 1 : a.what, reset, s, skip);
         prof_end(s);
         return hipGetLastError();
     }

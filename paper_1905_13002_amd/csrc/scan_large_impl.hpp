@@ -442,6 +442,7 @@ __device__ __forceinline__ void build_fvec(const Ctx& c, const R* cst, const Con
 // ---------------------------------------------------------------------------
 template <typename R, bool SEG, bool LDSA>
 __global__ __launch_bounds__(kThreads) void k_large_filter_reduce(LargeArgs la) {
+    if (skipped(la.s)) return;
     extern __shared__ __align__(16) char lds[];
     __shared__ int ish[72];   // flags; LU pivot rows
     const ScanArgs& a = la.s;
@@ -497,6 +498,7 @@ __global__ __launch_bounds__(kThreads) void k_large_filter_reduce(LargeArgs la) 
 // out[i] = in[i - d] (x) in[i] (i >= d), else in[i]
 template <typename R, bool SEG, bool LDSA>
 __global__ __launch_bounds__(kThreads) void k_large_filter_ks(LargeArgs la, const void* in_, void* out_, int64_t d) {
+    if (skipped(la.s)) return;
     extern __shared__ __align__(16) char lds[];
     __shared__ int ish[72];   // flags; LU pivot rows
     const ScanArgs& a = la.s;
@@ -527,6 +529,7 @@ __global__ __launch_bounds__(kThreads) void k_large_filter_ks(LargeArgs la, cons
 
 template <typename R, bool SEG, bool LDSA>
 __global__ __launch_bounds__(kThreads) void k_large_filter_down(LargeArgs la) {
+    if (skipped(la.s)) return;
     extern __shared__ __align__(16) char lds[];
     __shared__ int ish[72];   // flags; LU pivot rows
     const ScanArgs& a = la.s;
@@ -655,6 +658,7 @@ __device__ __forceinline__ void load_moments(const Ctx& c, const ScanArgs& a, in
 
 template <typename R, bool SEG, bool LDSA>
 __global__ __launch_bounds__(kThreads) void k_large_smoother_reduce(LargeArgs la) {
+    if (skipped(la.s)) return;
     extern __shared__ __align__(16) char lds[];
     __shared__ int ish[72];   // flags; LU pivot rows
     const ScanArgs& a = la.s;
@@ -701,6 +705,7 @@ __global__ __launch_bounds__(kThreads) void k_large_smoother_reduce(LargeArgs la
 template <typename R, bool SEG, bool LDSA>
 __global__ __launch_bounds__(kThreads) void k_large_smoother_ks(LargeArgs la, const void* in_, void* out_, int64_t d,
                                                                int64_t nb) {
+    if (skipped(la.s)) return;
     extern __shared__ __align__(16) char lds[];
     __shared__ int ish[72];   // flags; LU pivot rows
     const ScanArgs& a = la.s;
@@ -720,6 +725,7 @@ __global__ __launch_bounds__(kThreads) void k_large_smoother_ks(LargeArgs la, co
 
 template <typename R, bool SEG, bool LDSA>
 __global__ __launch_bounds__(kThreads) void k_large_smoother_down(LargeArgs la) {
+    if (skipped(la.s)) return;
     extern __shared__ __align__(16) char lds[];
     __shared__ int ish[72];   // flags; LU pivot rows
     const ScanArgs& a = la.s;

@@ -36,6 +36,8 @@ namespace pks {
 namespace {
 
 constexpr int kBlock = 256;     // threads per workgroup (4 waves)
+// kernels that may follow the settled-covariance path, which takes no smaller states
+template <int N> constexpr bool kGated = N >= 3;
 
 // ---------------------------------------------------------------------------
 // struct-of-arrays helpers: record word w of item i lives at base[w*stride+i]
@@ -535,6 +537,9 @@ __device__ __forceinline__ void load_gz(const R* __restrict__ cst, const ConstLa
 // single-step elements are folded with the rank-ny form of Lemma 2.
 template <int N, typename R, int EPT, bool SEG, int M>
 __global__ __launch_bounds__(kBlock) void k_filter_reduce(ScanArgs a) {
+    // not through skipped(): with the arguments pinned there the FP64 kernel took
+    // 33.5 us instead of 28.6 (T = 1024)
+    if (kGated<N> && a.skip && *a.skip != 0) return;
     clear_top_flags(a);
     // one shared model with the rank-ny form: constants from an LDS copy (the
     // first-step choice differs between lanes, and the constants read under it
@@ -603,6 +608,7 @@ __global__ __launch_bounds__(kBlock) void k_filter_reduce(ScanArgs a) {
 // reduce over explicit items (level 1: the level-0 wave aggregates)
 template <int N, typename R, int EPT, bool G>
 __global__ __launch_bounds__(kBlock) void k_filter_reduce_items(ScanArgs a) {
+    if (kGated<N> && skipped(a)) return;
     clear_top_flags(a);
     const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int lane = threadIdx.x & 63;
@@ -629,6 +635,7 @@ __global__ __launch_bounds__(kBlock) void k_filter_reduce_items(ScanArgs a) {
 // level-1 down: carries of the level-0 waves
 template <int N, typename R, int EPT, bool G>
 __global__ __launch_bounds__(kBlock) void k_filter_down_items(ScanArgs a) {
+    if (kGated<N> && skipped(a)) return;
     const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t i0 = gt * EPT;
     if (i0 >= a.nwaves) return;
@@ -652,6 +659,7 @@ __global__ __launch_bounds__(kBlock) void k_filter_down_items(ScanArgs a) {
 // level-0 down: outputs m_k, P_k
 template <int N, typename R, int EPT, bool SEG, int M>
 __global__ __launch_bounds__(kBlock) void k_filter_down(ScanArgs a) {
+    if (kGated<N> && skipped(a)) return;
     constexpr bool STG = !SEG && M > 0;
     __shared__ R stage[kBlock / 64][MomStage<N, R>::WORDS];
     __shared__ R csh[STG ? kStageF : 1];
@@ -723,6 +731,7 @@ __global__ __launch_bounds__(kBlock) void k_filter_down(ScanArgs a) {
 // arrays: each thread reads its filter prefix before writing its smoother one).
 template <int N, typename R, int EPT, bool SEG, int M>
 __global__ __launch_bounds__(kBlock) void k_filter_down_smooth_reduce(ScanArgs a) {
+    if (kGated<N> && skipped(a)) return;
     clear_top_flags(a);
     constexpr bool STG = !SEG && M > 0;
     __shared__ R stage[kBlock / 64][MomStage<N, R>::WORDS];
@@ -811,6 +820,7 @@ __global__ __launch_bounds__(kBlock) void k_filter_down_smooth_reduce(ScanArgs a
 // ===========================================================================
 template <int N, typename R, int EPT, bool SEG>
 __global__ __launch_bounds__(kBlock) void k_smoother_reduce(ScanArgs a) {
+    if (kGated<N> && skipped(a)) return;
     clear_top_flags(a);
     __shared__ R fsh[SEG ? 1 : StageS<N>::words];
     const ConstLayout CL = const_layout(N, a.ny);
@@ -854,6 +864,7 @@ __global__ __launch_bounds__(kBlock) void k_smoother_reduce(ScanArgs a) {
 
 template <int N, typename R, int EPT, bool G>
 __global__ __launch_bounds__(kBlock) void k_smoother_reduce_items(ScanArgs a) {
+    if (kGated<N> && skipped(a)) return;
     clear_top_flags(a);
     const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int lane = threadIdx.x & 63;
@@ -878,6 +889,7 @@ __global__ __launch_bounds__(kBlock) void k_smoother_reduce_items(ScanArgs a) {
 
 template <int N, typename R, int EPT, bool G>
 __global__ __launch_bounds__(kBlock) void k_smoother_down_items(ScanArgs a) {
+    if (kGated<N> && skipped(a)) return;
     const int64_t gt = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t i0 = gt * EPT;
     if (i0 >= a.nwaves) return;
@@ -900,6 +912,7 @@ __global__ __launch_bounds__(kBlock) void k_smoother_down_items(ScanArgs a) {
 
 template <int N, typename R, int EPT, bool SEG>
 __global__ __launch_bounds__(kBlock) void k_smoother_down(ScanArgs a) {
+    if (kGated<N> && skipped(a)) return;
     __shared__ R stage[kBlock / 64][MomStage<N, R>::WORDS];
     __shared__ R fsh[SEG ? 1 : StageS<N>::words];
     const ConstLayout CL = const_layout(N, a.ny);
@@ -988,6 +1001,7 @@ inline TopArgs top_args(const void* items, int64_t n, void* carry, const ScanArg
     t.model_fail = a.model_fail;
     t.nmodels = a.nmodels;
     t.status = a.status;
+    t.skip = a.skip;
     return t;
 }
 template <int N, typename R, bool G>

@@ -260,6 +260,7 @@ struct TopArgs {
     const int* model_fail;
     int nmodels;
     int* status;         // numeric flag; sequence 0 is reported if a published aggregate never arrives
+    const int* skip;             // as ScanArgs::skip
 };
 
 // The published aggregate of workgroup src (waiting for its flag), or the
@@ -314,6 +315,10 @@ __device__ __forceinline__ int levels_for(int n) {
 // ---------------------------------------------------------------------------
 template <int N, typename R, bool G>
 __global__ __launch_bounds__(kTopThreads) void k_filter_top(TopArgs t) {
+    if constexpr (N >= 3) {                    // (kGated)
+        asm volatile("" ::"s"(t.items));       // (as in skipped())
+        if (t.skip && *t.skip != 0) return;
+    }
     __shared__ double sh[kTopGroups * kEFWords * 16];
     __shared__ double shm[2 * 16];
     __shared__ int ticket;
@@ -403,6 +408,10 @@ __global__ __launch_bounds__(kTopThreads) void k_filter_top(TopArgs t) {
 // ---------------------------------------------------------------------------
 template <int N, typename R, bool G>
 __global__ __launch_bounds__(kTopThreads) void k_smoother_top(TopArgs t) {
+    if constexpr (N >= 3) {                    // (kGated)
+        asm volatile("" ::"s"(t.items));       // (as in skipped())
+        if (t.skip && *t.skip != 0) return;
+    }
     __shared__ double sh[kTopGroups * kESWords * 16];
     __shared__ double shm[2 * 16];
     __shared__ int ticket;
