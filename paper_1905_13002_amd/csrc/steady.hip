@@ -13,77 +13,12 @@
 #include <algorithm>
 #include <cstdint>
 
-#include "steady.hpp"
-#include "tile16.hpp"
+#include "steady_ops.hpp"
 
 namespace pks {
 namespace steady {
 
-using namespace w16;
-
 namespace {
-
-// how small |A|^2 |P| has to be against |C|: FP64 rounding with 2^7 to spare
-// for covariances of the head above the prior and the settled one (checked
-// when the head is formed)
-constexpr double kTiny = 8.673617379884035e-19;      // 2^-60
-constexpr double kSpare = 128.0;
-
-// ---------------------------------------------------------------------------
-// tiles with KX (KY) K-slices: rows and columns beyond 4 KX are zero
-// ---------------------------------------------------------------------------
-// columns moved by D (zero enters): lane i takes lane i - D (up) or i + D (down) of its row of 16
-template <int CTRL>
-__device__ __forceinline__ double dpp0(double x) {
-    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, false);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, false);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-template <bool UP, int D, int KX>
-__device__ __forceinline__ f64x4 shift(const f64x4& x) {
-    f64x4 t = zero4();
-#pragma unroll
-    for (int v = 0; v < KX; ++v) t[v] = UP ? dpp0<0x110 + D>(x[v]) : dpp0<0x100 + D>(x[v]);
-    return t;
-}
-__device__ __forceinline__ double wave_sum(double x) {
-    x += dpp0<0x111>(x);
-    x += dpp0<0x112>(x);
-    x += dpp0<0x114>(x);
-    x += dpp0<0x118>(x);         // the last lane of every row of 16 holds the row's sum
-    return (readlane_d(x, 15) + readlane_d(x, 31)) + (readlane_d(x, 47) + readlane_d(x, 63));
-}
-__device__ __forceinline__ double sumsq(const f64x4& t) {
-    return wave_sum(fma(t[0], t[0], t[1] * t[1]) + fma(t[2], t[2], t[3] * t[3]));
-}
-
-// Inverse by Gauss-Jordan elimination without pivoting, as w16::inv_diag, with
-// a constant number NP of pivots (rows beyond the matrix hold the identity), so
-// that no branch keeps the compiler from overlapping it with other work.
-template <int NP, bool SPD>
-__device__ __forceinline__ f64x4 inv_np(f64x4 a, bool& ok) {
-    const int li = lane_i(), lk = lane_k();
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-        const int q = k >> 2, g = k & 3;
-        const double pv = readlane_d(a[q], (g << 4) | k);
-        double ck[4];
-#pragma unroll
-        for (int v = 0; v < NP / 4; ++v) ck[v] = col_bcast(a[v], k);
-        const double rk = row_bcast(a[q], g);
-        ok = ok && (SPD ? pv > 0.0 : pv != 0.0) && isfinite(pv);
-        const double r = recip(pv);
-        const double rr = rk * r;
-#pragma unroll
-        for (int v = 0; v < NP / 4; ++v) {
-            const double f = ck[v] * r;
-            if (4 * v + lk == k) a[v] = li == k ? r : rr;
-            else a[v] = li == k ? -f : fma(-f, rk, a[v]);
-        }
-    }
-    return a;
-}
 
 // (M^T)^-1 for M = I + C J given the tiles of C and J: unpivoted, kept when its
 // residual is below 1e-11 in every entry, else with partial pivoting
@@ -442,94 +377,6 @@ __device__ __forceinline__ void head_fill(const Args& a, int i, double* st) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// sequences
-// ---------------------------------------------------------------------------
-struct SeqR {
-    int b;
-    int64_t start, end;
-};
-__device__ __forceinline__ SeqR seq_of(const Args& a, int b) {
-    if (!a.offsets) return SeqR{0, 0, a.total};
-    return SeqR{b, a.offsets[b], a.offsets[b + 1]};
-}
-__device__ __forceinline__ int seq_holding(const int64_t* off, int B, int64_t k) {     // off[b] <= k < off[b + 1]
-    int lo = 0, hi = B;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (off[mid] <= k) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-// ---------------------------------------------------------------------------
-// covariance rows of all steps, from the tables, by the workgroups of a launch
-// that are left (wg of nwg).  Bound by the HBM writes: consecutive threads on
-// consecutive 16-byte units of a contiguous range of rows, streaming stores;
-// the settled row comes from LDS.
-// ---------------------------------------------------------------------------
-template <typename R, int BYTES> struct Unit;
-template <typename R> struct Unit<R, 16> { using T = unsigned __attribute__((ext_vector_type(4))); };
-template <typename R> struct Unit<R, 8> { using T = unsigned __attribute__((ext_vector_type(2))); };
-template <typename R> struct Unit<R, 4> { using T = unsigned; };
-
-template <typename R, int BYTES, bool SMOOTHED>
-__device__ __forceinline__ void write_rows_u(const Args& a, int nh, int64_t wg, int64_t nwg, R* lds) {
-    using UT = typename Unit<R, BYTES>::T;
-    constexpr int V = BYTES / (int)sizeof(R);
-    const int n = a.nx, n2 = n * n;
-    const double* settled = a.star + (SMOOTHED ? star_Ps(n, a.ny) : star_P(n, a.ny));
-    for (int i = threadIdx.x; i < n2; i += blockDim.x) lds[i] = R(settled[i]);
-    __syncthreads();
-    R* dst = static_cast<R*>(SMOOTHED ? a.Ps : a.P);
-    const int upr = n2 / V, S = blockDim.x;
-    const int64_t per = (a.total + nwg - 1) / nwg;
-    const int64_t r0 = wg * per, r1 = r0 + per < a.total ? r0 + per : a.total;
-    int64_t row = r0 + threadIdx.x / upr;
-    int off = threadIdx.x % upr;
-    const int srow = S / upr, soff = S % upr;
-    if (row >= r1) return;
-    int b = a.offsets ? seq_holding(a.offsets, a.B, row) : 0;
-    SeqR q = seq_of(a, b);
-    UT* out = reinterpret_cast<UT*>(dst);
-    while (row < r1) {
-        while (row >= q.end) q = seq_of(a, q.b + 1);
-        const int64_t k = row - q.start, len = q.end - q.start;
-        UT v;
-        bool mine = true;
-        const double* src = nullptr;
-        if (!SMOOTHED) {
-            if (k < nh - 1) src = a.tP + k * n2;
-        } else if (len < 2 * nh && k < nh - 1) {
-            mine = false;                        // a short sequence's head is its own (short_head)
-        } else if (k < nh - 1) {
-            src = a.tHead + k * n2;
-        } else if (len - 1 - k < nh - 1) {
-            src = a.tTail + (len - 1 - k) * n2;
-        }
-        if (src) {
-            R t[V];
-#pragma unroll
-            for (int i = 0; i < V; ++i) t[i] = R(src[off * V + i]);
-            __builtin_memcpy(&v, t, BYTES);
-        } else {
-            __builtin_memcpy(&v, lds + off * V, BYTES);
-        }
-        if (mine) __builtin_nontemporal_store(v, out + row * upr + off);
-        row += srow;
-        off += soff;
-        if (off >= upr) {
-            off -= upr;
-            ++row;
-        }
-    }
-}
-template <typename R, bool SMOOTHED>
-__device__ __forceinline__ void write_rows(const Args& a, int nh, int64_t wg, int64_t nwg, R* lds) {
-    if ((a.nx & 1) == 0) write_rows_u<R, 16, SMOOTHED>(a, nh, wg, nwg, lds);
-    else write_rows_u<R, sizeof(R), SMOOTHED>(a, nh, wg, nwg, lds);
-}
-
 // A sequence shorter than 2 n: its smoothed head covariances depend on its
 // length and are folded one by one (Lemma 4) from its own last ones.
 template <typename R, int KX>
@@ -567,34 +414,6 @@ __device__ __forceinline__ void short_head(const Args& a, int nh, int b, double*
 // a tile, the 4 tiles of a workgroup, 16 workgroups, and those one after
 // another.
 // ---------------------------------------------------------------------------
-// column of a tile <-> vector of n in memory
-template <int KX, typename T>
-__device__ __forceinline__ f64x4 load_col(const T* x, int n) {
-    const int lk = lane_k();
-    f64x4 t = zero4();
-#pragma unroll
-    for (int v = 0; v < KX; ++v)
-        if (4 * v + lk < n) t[v] = double(x[4 * v + lk]);
-    return t;
-}
-template <int KX, typename T>
-__device__ __forceinline__ void store_col(T* x, const f64x4& t, int n) {
-    const int lk = lane_k();
-#pragma unroll
-    for (int v = 0; v < KX; ++v)
-        if (4 * v + lk < n) x[4 * v + lk] = T(t[v]);
-}
-// operand of a product with the n x m matrix X from the left: the tile of X^T
-template <int KX>
-__device__ __forceinline__ f64x4 load_op(const double* X, int n, int m) {
-    const int li = lane_i(), lk = lane_k();
-    f64x4 t = zero4();
-#pragma unroll
-    for (int v = 0; v < KX; ++v)
-        if (li < n && 4 * v + lk < m) t[v] = X[li * m + 4 * v + lk];
-    return t;
-}
-
 // inclusive scan over the columns with the matrix M whose powers 1, 2, 4, 8
 // are at mp: X_c <- X_c + M X_{c-1} + M^2 X_{c-2} + ... (UP; else over c + 1, ...)
 template <int KX, bool UP>
@@ -631,27 +450,6 @@ __device__ __forceinline__ Chain chain_of(const Args& a, int nh, int64_t blk, in
     c.len = q.end - q.start;
     c.k0 = nh + (((blk - a.blk_off[b]) * kBlockChains + wave * 16 + lane_i()) << a.pL);
     return c;
-}
-
-// the sequence of this lane's column in a group of 16 (heads)
-struct Head {
-    int64_t start;
-    int len, b;            // steps, at most nh (0: no sequence)
-    int64_t full;
-};
-__device__ __forceinline__ Head head_of(const Args& a, int nh, int group) {
-    Head h;
-    h.b = group * 16 + lane_i();
-    const bool live = h.b < a.B;
-    if (!live) h.b = a.B - 1;
-    const SeqR q = seq_of(a, h.b);
-    h.start = q.start;
-    h.full = live ? q.end - q.start : 0;
-    h.len = (int)(h.full < nh ? h.full : nh);
-    return h;
-}
-__device__ __forceinline__ double* run_vec(const Args& a, double* base, int b, int run) {
-    return base + ((int64_t)b * (a.N / kRun) + run) * a.nx;
 }
 
 // m at the kRun steps of a head run, from X; rows[] gets the means as stored
@@ -1130,16 +928,18 @@ constexpr int64_t kMinSteps = 8192, kMinMean = 1024;
 constexpr int64_t kMinWorkF64 = 6 << 20, kMinWorkF32 = 12 << 20;     // T nx^3, nx <= 4
 
 bool applies(int nx, int ny, int32_t B, int64_t total, bool mixed) {
-    if (nx > 16 || ny > 16 || total < kMinSteps || total / B < kMinMean) return false;
+    if (ny > (nx + 15) / 16 * 16 || total < kMinSteps || total / B < kMinMean) return false;
     return nx > 4 || (nx > 2 && total * nx * nx * nx >= (mixed ? kMinWorkF32 : kMinWorkF64));
 }
 
 bool layout(Args& a, char* base, size_t bytes) {
     const int64_t n = a.nx, m = a.ny, n2 = n * n;
     // at least 16 steps a chain, at most 32768 chains (2048 waves)
+    const bool large = a.nx > 16;        // 16 chains a workgroup, at most 16384
     a.pL = 4;
-    while ((a.total >> a.pL) > 32768) ++a.pL;
-    a.max_blocks = a.total / (kBlockChains << a.pL) + a.B;
+    while ((a.total >> a.pL) > (large ? 16384 : 32768)) ++a.pL;
+    const int64_t chains = large ? 16 : kBlockChains;
+    a.max_blocks = a.total / (chains << a.pL) + a.B;
     for (a.N = 1024; a.N >= 64; a.N /= 2) {
         if (a.N > a.total / a.B / 4) continue;
         char* p = base;
@@ -1168,8 +968,12 @@ bool layout(Args& a, char* base, size_t bytes) {
         a.runPhi = take(runs * n2);
         a.runE = take(runs * n2);
         a.runL = take(runs * n2);
-        a.runC = take(runs * n2);
-        a.pre = take(a.max_blocks * kBlockChains * n);
+        a.runC = large ? nullptr : take(runs * n2);
+        for (int i = 0; i < 2; ++i) {
+            a.scanE[i] = large ? take(runs * n2) : nullptr;
+            a.scanL[i] = large ? take(runs * n2) : nullptr;
+        }
+        a.pre = take(a.max_blocks * chains * n);
         a.agg = take(a.max_blocks * n);
         a.car = take(a.max_blocks * n);
         a.runB = take(a.B * runs * n);
@@ -1179,7 +983,10 @@ bool layout(Args& a, char* base, size_t bytes) {
     return false;
 }
 
-hipError_t launch(Args a, bool mixed, hipStream_t s) { return mixed ? run_kx<float>(a, s) : run_kx<double>(a, s); }
+hipError_t launch(Args a, bool mixed, hipStream_t s) {
+    if (a.nx > 16) return launch_large(a, mixed, s);
+    return mixed ? run_kx<float>(a, s) : run_kx<double>(a, s);
+}
 
 }  // namespace steady
 }  // namespace pks

@@ -49,6 +49,7 @@ struct Args {
     double *mpF, *mpE;           // [kPowers][n^2] Phi^(L 2^i), E^(L 2^i)
     double *tP, *tPhi, *tK, *tc, *tE, *tL, *tHead, *tTail;     // [N] tables
     double *runPhi, *runE, *runL, *runC;   // [N / kRun] of a run: Phi, smoothing element, smoothed covariance that enters
+    double *scanE[2], *scanL[2];           // nx > 16: suffix scan of the runs' smoothing elements
     double *pre, *agg, *car;     // [chains][n], [blocks][n]: what chains and blocks add, what enters blocks
     double *runB, *runX;         // [B][N / kRun][n]: what a run of a head adds, what enters it
     int64_t max_blocks;
@@ -68,6 +69,7 @@ __host__ __device__ inline int64_t star_c(int n, int m) { return 5 * (int64_t)n 
 bool applies(int nx, int ny, int32_t B, int64_t total, bool mixed);
 bool layout(Args& a, char* base, size_t bytes);
 hipError_t launch(Args a, bool mixed, hipStream_t s);
+hipError_t launch_large(const Args& a, bool mixed, hipStream_t s);       // 16 < nx <= 64
 
 }  // namespace steady
 }  // namespace pks

@@ -1,6 +1,6 @@
-"""Time-invariant models whose covariances settle (csrc/steady.hip): the path
+"""Time-invariant models whose covariances settle (csrc/steady*.hip): the path
 taken (a word of the workspace's status block), every step against the oracle
-at the parity bars, over state and measurement sizes up to a tile, lengths
+at the parity bars, over state and measurement sizes, lengths
 around the edges of chains and blocks, packed sequences shorter and longer than
 the head, and models that do not settle, which the general scan takes."""
 import json
@@ -51,7 +51,8 @@ def against_oracle(out, model, y, precision, offsets=None):
 
 
 @pytest.mark.parametrize("nx,ny,T", [(3, 1, 466101), (4, 2, 196609), (4, 4, 196700), (4, 16, 262143), (5, 5, 8192), (7, 2, 9001), (8, 8, 12345), (9, 4, 8255), (12, 16, 8200), (13, 5, 16384),
-                                     (16, 16, 8193), (16, 3, 20011)])
+                                     (16, 16, 8193), (16, 3, 20011),
+                                     (17, 32, 8200), (24, 10, 9001), (33, 5, 8192), (48, 48, 8193), (64, 32, 8209), (64, 64, 8192)])
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_sizes(pks, nx, ny, T, precision):
     rng = np.random.default_rng(100 * nx + ny)
@@ -65,7 +66,7 @@ def test_sizes(pks, nx, ny, T, precision):
     assert np.array_equal(out["ms"][-1], out["m"][-1]) and np.array_equal(out["Ps"][-1], out["P"][-1])
 
 
-@pytest.mark.parametrize("nx,ny,long", [(4, 2, 200000), (6, 6, 20000), (16, 5, 20000)])
+@pytest.mark.parametrize("nx,ny,long", [(4, 2, 200000), (6, 6, 20000), (16, 5, 20000), (20, 6, 20000), (50, 20, 20000)])
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_packed(pks, nx, ny, long, precision):
     """Sequences of 0 and 1 steps, up to, at and beyond the head, between the
@@ -101,7 +102,7 @@ def slow_model(nx):
     return wl.Model(np.eye(nx), 1e-8 * np.eye(nx), np.eye(nx), np.eye(nx), np.ones(nx), np.eye(nx))
 
 
-@pytest.mark.parametrize("model,T", [(slow_model(4), 100000), (slow_model(6), 9000),
+@pytest.mark.parametrize("model,T", [(slow_model(4), 100000), (slow_model(6), 9000), (slow_model(20), 8192),
                                      (wl.Model(np.eye(3), np.zeros((3, 3)), np.eye(3)[:2], 0.5 * np.eye(2), np.zeros(3),
                                                np.eye(3)), 240000)])
 def test_models_that_do_not_settle(pks, model, T):
@@ -123,7 +124,7 @@ def test_general_scan_configurations(pks, tmp_path, monkeypatch, ept, ept1):
     against_oracle(out, model, y, "fp64")
 
 
-@pytest.mark.parametrize("nx", [4, 9])
+@pytest.mark.parametrize("nx", [4, 9, 20])
 def test_priors(pks, nx):
     """A known start (P0 = 0) and one far above the settled covariance (the
     oracle's own update P - K S K^T loses |P0|^2 of the rounding: 6e-6 at 1e6 I
