@@ -13,6 +13,7 @@
 
 #include "pks_internal.h"
 #include "plan.h"
+#include "chains.hpp"
 #include "steady.hpp"
 
 namespace pks {
@@ -233,6 +234,27 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
         if (steady::layout(t, base + r0, r1 - r0)) {
             e = steady::launch(t, mixed, s);
             if (e != hipSuccess) return hip_fail(e, "settled-covariance kernels");
+            skip = t.ctl;
+        }
+    }
+    // time-varying models: overlapped chains, verified on the device, the same way
+    if ((passes & 1) && tv && chains::applies(model.nx, model.ny, B, total, mixed)) {
+        char* base = static_cast<char*>(ws);
+        chains::Args t{};
+        t.nx = model.nx; t.ny = model.ny; t.B = B;
+        t.total = total;
+        t.offsets = offsets;
+        t.smooth = (passes & 2) != 0;
+        t.reset = 1;
+        t.each = model.per_sequence;
+        t.F = model.F; t.u = model.u; t.Q = model.Q; t.H = model.H; t.d = model.d; t.R = model.R;
+        t.m0 = model.m0; t.P0 = model.P0;
+        t.y = y; t.m = m; t.P = P; t.ms = ms; t.Ps = Ps;
+        t.status = reinterpret_cast<int*>(base + L.status);
+        t.ctl = t.status + kSteadyCtl;
+        if (chains::layout(t, base + L.thr, L.top_agg - L.thr)) {
+            e = chains::launch(t, mixed, s);
+            if (e != hipSuccess) return hip_fail(e, "overlapped-chain kernels");
             skip = t.ctl;
         }
     }
