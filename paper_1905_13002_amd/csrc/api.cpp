@@ -237,8 +237,10 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
             skip = t.ctl;
         }
     }
-    // time-varying models: overlapped chains, verified on the device, the same way
-    if ((passes & 1) && tv && chains::applies(model.nx, model.ny, B, total, mixed)) {
+    // models that change at every step, or one per sequence: overlapped chains,
+    // verified on the device, the same way
+    if ((passes & 1) && (tv || model.per_sequence) &&
+        chains::applies(model.nx, model.ny, B, total, mixed, tv, (passes & 2) != 0)) {
         char* base = static_cast<char*>(ws);
         chains::Args t{};
         t.nx = model.nx; t.ny = model.ny; t.B = B;
@@ -252,8 +254,8 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
         t.y = y; t.m = m; t.P = P; t.ms = ms; t.Ps = Ps;
         t.status = reinterpret_cast<int*>(base + L.status);
         t.ctl = t.status + kSteadyCtl;
-        if (chains::layout(t, base + L.thr, L.top_agg - L.thr)) {
-            e = chains::launch(t, mixed, s);
+        if (chains::layout(t, base + L.thr, L.top_agg - L.thr, tv)) {
+            e = chains::launch(t, mixed, tv, s);
             if (e != hipSuccess) return hip_fail(e, "overlapped-chain kernels");
             skip = t.ctl;
         }

@@ -18,6 +18,9 @@ namespace {
 
 constexpr int kAhead = 4;            // steps of a group; their loads are issued a group or two before
 constexpr double kSame = 5.684341886080802e-14;       // 2^-44
+constexpr double kTiny = 8.673617379884035e-19;       // 2^-60
+constexpr int kMaxLog = 9;           // settled after at most 2^kMaxLog steps
+constexpr int kLongest = 384;        // and no later than this (a step of a head is 0.33 us of the filter, 0.5 of the smoother)
 
 struct Lane {
     int j, b, i;
@@ -91,6 +94,30 @@ __device__ __forceinline__ bool positive(double x, const Lane& t) {
     }
     return ok;
 }
+// the inverse of a general N x N block, its pivots on the diagonal
+template <int P>
+__device__ __forceinline__ double pivot(double x, const Lane& t, bool& ok) {
+    const double rp = row<P>(x, t), cp = col<P>(x), pv = col<P>(rp);
+    ok &= fabs(pv) > 0.0;
+    const double r = w16::recip(pv);
+    const double rr = t.j == P ? r : rp * r;
+    const double v = fma(-cp, rr, t.j == P ? 0.0 : x);
+    return t.i == P ? rr : v;
+}
+template <int N>
+__device__ __forceinline__ double inv_general(double x, const Lane& t, bool& ok) {
+    x = pivot<0>(x, t, ok);
+    if constexpr (N > 1) x = pivot<1>(x, t, ok);
+    if constexpr (N > 2) x = pivot<2>(x, t, ok);
+    if constexpr (N > 3) x = pivot<3>(x, t, ok);
+    return x;
+}
+// sum of the squares of a tile, on every lane of the chain
+__device__ __forceinline__ double sumsq(double x, const Lane& t) {
+    const double g = mm(x, x);               // its diagonal: the columns' sums of squares
+    return mm(1.0, mm(t.i == t.j ? g : 0.0, 1.0));
+}
+
 // ---------------------------------------------------------------------------
 // where a lane finds its entries of a model's arrays
 // ---------------------------------------------------------------------------
@@ -131,13 +158,12 @@ struct Rows {
         step = words * (unsigned)sizeof(T);
         at = on ? (unsigned)((k - k0) * step) + lane_at * (unsigned)sizeof(T) : kOutside;
     }
-    __device__ __forceinline__ double get(int s) const {
-        if constexpr (sizeof(T) == 8) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)at, (int)(s * step), 0);
-            return __builtin_bit_cast(double, v);
-        } else {
-            return (double)__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)at, (int)(s * step), 0));
-        }
+    // (as it is stored: a conversion here would wait for the load)
+    __device__ __forceinline__ T get(int s) const {
+        if constexpr (sizeof(T) == 8)
+            return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)at, (int)(s * step), 0));
+        else
+            return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)at, (int)(s * step), 0));
     }
     __device__ __forceinline__ void put(int s, double x, bool on) const {
         const int o = (int)(on ? at : kOutside), so = (int)(s * step);
@@ -171,15 +197,10 @@ __device__ __forceinline__ Chain chain_of(const Args& a, int64_t c) {
     x.hi = a.total;
     int64_t before = 0;
     if (a.offsets) {
-        int lo = 0, hi = a.B;                // first[lo] <= c < first[hi]
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (a.first[mid] <= x.c) lo = mid; else hi = mid;
-        }
-        x.b = lo;
-        x.lo = a.offsets[lo];
-        x.hi = a.offsets[lo + 1];
-        before = a.first[lo];
+        x.b = a.sequence[x.c];
+        x.lo = a.offsets[x.b];
+        x.hi = a.offsets[x.b + 1];
+        before = a.first[x.b];
     }
     x.s = x.lo + (x.c - before) * a.l;
     x.e = min(x.s + a.l, x.hi);
@@ -244,11 +265,13 @@ __device__ __forceinline__ void store_state(double* p, int64_t c, const Lane& t,
 }
 
 // ---------------------------------------------------------------------------
-// The flags, and the chains of every packed sequence.
+// The flags, and the chains of every packed sequence.  (A chain's wave reads its
+// sequence from a table: a search would be ten loads in a row.)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_chain_setup(Args a) {
-    const int lane = threadIdx.x;
-    if (lane == 0) {
+__global__ __launch_bounds__(1024) void k_chain_setup(Args a) {
+    __shared__ int64_t part[16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (tid == 0) {
         if (a.reset || a.status[1] != kStatusMagic) {
             a.status[0] = kStatusOk;
             a.status[1] = kStatusMagic;
@@ -257,19 +280,161 @@ __global__ __launch_bounds__(64) void k_chain_setup(Args a) {
     }
     if (!a.offsets) return;
     int64_t before = 0;
-    for (int b0 = 0; b0 < a.B; b0 += 64) {
-        const int b = b0 + lane;
+    for (int b0 = 0; b0 < a.B; b0 += 1024) {
+        const int b = b0 + tid;
         const int64_t own = b < a.B ? (a.offsets[b + 1] - a.offsets[b] + a.l - 1) / a.l : 0;
         int64_t inc = own;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
-            const int64_t v = __shfl_up(inc, d, 64);
+            const int64_t v = __shfl_up((long long)inc, d, 64);
             if (lane >= d) inc += v;
         }
-        if (b < a.B) a.first[b] = before + inc - own;
-        before += __shfl(inc, 63, 64);
+        if (lane == 63) part[w] = inc;
+        __syncthreads();
+        int64_t ahead = before;
+        for (int i = 0; i < 16; ++i) {
+            if (i < w) ahead += part[i];
+            before += part[i];
+        }
+        __syncthreads();
+        if (b < a.B) {
+            const int64_t c0 = ahead + inc - own;
+            a.first[b] = c0;
+            for (int64_t c = c0; c < c0 + own; ++c) a.sequence[c] = b;
+        }
     }
-    if (lane == 0) a.first[a.B] = before;
+    if (tid == 0) a.first[a.B] = before;
+}
+
+// ---------------------------------------------------------------------------
+// Settled covariances of time-invariant models, four a wave: the filtering
+// element of one step is doubled (Lemma 2 on equal elements) until
+// |A|^2 (|P0| + |C|) <= 2^-60 |C|, after which every filtered covariance is C to
+// the last bit of FP64, and the smoothing element (Lemma 4) the same way; the
+// powers then give the number of steps to 16.
+// Bound by the latency of up to 2 kMaxLog dependent combines.
+// ---------------------------------------------------------------------------
+template <int NX, int NY>
+__global__ __launch_bounds__(64) void k_chain_models(Args a) {
+    const Lane t = lane_of();
+    const int q = (int)blockIdx.x * 4 + t.b, b = q < a.B ? q : a.B - 1;
+    const At at = at_of(t, a.nx, a.ny);
+    const int64_t n2 = a.nx * a.nx, nm = a.nx * a.ny, m2 = a.ny * a.ny;
+    const double FT = pick(at.nn, a.F[b * n2 + at.ft]), F = pick(at.nn, a.F[b * n2 + at.q]);
+    const double Q = pick(at.nn, a.Q[b * n2 + at.q]), HT = pick(at.mn, a.H[b * nm + at.ht]);
+    const double R = pick(at.mm, a.R[b * m2 + at.r]), P0 = pick(at.nn, a.P0[b * n2 + at.q]);
+    const double u = a.u ? pick(at.n, a.u[(int64_t)b * a.nx + at.v]) : 0.0;
+    const double d = a.d ? pick(at.m, a.d[(int64_t)b * a.ny + at.w]) : 0.0;
+    const double I = t.i == t.j && t.i < a.nx ? 1.0 : 0.0;
+    bool ok = true;
+    double A, C, J;
+    {
+        const double QH = mm(Q, HT), HQ = mm(HT, Q), Si = inv<NY>(mm(HT, QH, R), t, ok);
+        const double Kt = mm(Si, HQ), G = mm(HT, F);
+        A = mm(-Kt, G, F);
+        C = sym(mm(-Kt, HQ, Q), t);
+        J = sym(mm(G, mm(Si, G)), t);
+    }
+    const double p0 = sqrt(sumsq(P0, t));
+    int lf = -1, le = -1;
+    __shared__ double lev[kMaxLog][3][64];            // A, C, J of 2^l steps
+    const int lane = threadIdx.x;
+    auto combine = [&](double Ai, double Ci, double Aj, double Cj, double Jj, double& An, double& Cn, double& X, bool& fine) {
+        const double M = mm(Ci, Jj, I);                       // I + C_i J_j
+        X = inv_general<NX>(M, t, fine);
+        // one Newton step: the elimination has no row exchanges
+        X = mm(trans(X, t), I - mm(trans(M, t), X), X);
+        const double AX = mm(trans(Aj, t), X);                // A_j (I + C_i J_j)^-1
+        An = mm(trans(AX, t), Ai);
+        Cn = sym(mm(trans(mm(trans(AX, t), Ci), t), trans(Aj, t), Cj), t);
+    };
+    auto settled = [&](double An, double Cn) {
+        const double fa = sumsq(An, t), fc = sqrt(sumsq(Cn, t));
+        return fa * (p0 + fc) <= kTiny * fc;
+    };
+    for (int l = 1; l <= kMaxLog; ++l) {
+        lev[l - 1][0][lane] = A;
+        lev[l - 1][1][lane] = C;
+        lev[l - 1][2][lane] = J;
+        bool fine = true;
+        double An, Cn, X;
+        combine(A, C, A, C, J, An, Cn, X, fine);
+        const double JA = mm(J, A), Jn = sym(mm(JA, mm(trans(X, t), A), J), t);      // A^T J (I + C J)^-1 A + J
+        const bool on = lf < 0, good = settled(An, Cn);
+        ok &= fine || !on;
+        A = on ? An : A;
+        C = on ? Cn : C;
+        J = on ? Jn : J;
+        if (on && l >= 2 && good) lf = l;
+        if (!__any(lf < 0)) break;
+    }
+    // the smallest multiple of 16 steps after which they have: 2^(lf - 1) have not
+    int n16 = 16;
+    {
+        double Ac = 0.0, Cc = 0.0;
+        for (int l = kMaxLog - 1; l >= 4; --l) {
+            bool fine = true;
+            double An, Cn, X;
+            combine(Ac, Cc, lev[l][0][lane], lev[l][1][lane], lev[l][2][lane], An, Cn, X, fine);
+            const bool start = l == lf - 1, on = l < lf - 1 && !settled(An, Cn);
+            Ac = start ? lev[l][0][lane] : (on ? An : Ac);
+            Cc = start ? lev[l][1][lane] : (on ? Cn : Cc);
+            n16 += start || on ? 1 << l : 0;
+        }
+    }
+    // settled gains
+    const double P = C, W = mm(P, FT), Pp = sym(mm(FT, W, Q), t), VT = mm(HT, Pp);
+    const double Kt = mm(inv<NY>(mm(HT, mm(Pp, HT), R), t, ok), VT);
+    const double Phi = mm(-Kt, mm(HT, F), F), c = mm(-Kt, mm(HT, u, d), u);
+    double ET, p2, m_;
+    smoother_gain<NX>(FT, Q, 0.0, 0.0, P, t, ET, p2, m_, ok);
+    double E2 = ET, L;
+    {
+        const double EFP = mm(ET, mm(FT, P));
+        L = sym(P - EFP, t);
+    }
+    const double fp = sqrt(sumsq(P, t));
+    for (int l = 1; l <= kMaxLog; ++l) {
+        lev[l - 1][0][lane] = E2;
+        lev[l - 1][1][lane] = L;
+        const double Ln = sym(mm(E2, mm(L, E2), L), t), En = mm(trans(E2, t), E2);     // (E E)^T
+        const double fe = sumsq(En, t), fl = sqrt(sumsq(Ln, t));
+        const bool on = le < 0;
+        L = on ? Ln : L;
+        E2 = on ? En : E2;
+        if (on && l >= 2 && fe * fp <= kTiny * fl) le = l;
+        if (!__any(le < 0)) break;
+    }
+    int e16 = 16;
+    {
+        double Ec = 0.0, Lc = 0.0;
+        for (int l = kMaxLog - 1; l >= 4; --l) {
+            const double El = lev[l][0][lane], Ll = lev[l][1][lane];
+            const double Ln = sym(mm(Ec, mm(Ll, Ec), Lc), t), En = mm(trans(El, t), Ec);   // E_c L_l E_c^T + L_c, (E_c E_l)^T
+            const double fe = sumsq(En, t), fl = sqrt(sumsq(Ln, t));
+            const bool start = l == le - 1, on = l < le - 1 && !(fe * fp <= kTiny * fl);
+            Ec = start ? El : (on ? En : Ec);
+            Lc = start ? Ll : (on ? Ln : Lc);
+            e16 += start || on ? 1 << l : 0;
+        }
+    }
+    const double PhiT = trans(Phi, t);
+    if (q >= a.B) return;
+    double* o = a.model + (int64_t)b * kModel + 4 * t.i + t.j;
+    o[0] = PhiT;
+    o[16] = Kt;
+    o[32] = c;
+    o[48] = P;
+    o[64] = ET;
+    o[80] = L;
+    ok = ok && lf > 0 && le > 0;
+    const unsigned long long off = __ballot(!ok);
+    if (t.i == 0 && t.j == 0) {
+        const bool good = (off & (0x000f000f000f000full << (4 * t.b))) == 0 && n16 <= kLongest && e16 <= kLongest;
+        if (!good) a.ctl[0] = 0;
+        a.head[2 * b] = good ? n16 : 0;
+        a.head[2 * b + 1] = good ? e16 : 0;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -321,11 +486,14 @@ __global__ __launch_bounds__(64) void k_chain_filter_tv(Args a, int pass) {
     om.open(static_cast<const T*>(a.m), a.nx, a.total, kb, k0, at.n, at.v);
     oP.open(static_cast<const T*>(a.P), n2, a.total, kb, k0, at.nn, at.q);
     bool ok = true;
-    Row g[3][kAhead];
-    auto fetch = [&](Row (&r)[kAhead]) {
+    struct In {
+        double FT, Q, HT, R, u, d;
+        T y;
+    } g[3][kAhead];
+    auto fetch = [&](In (&r)[kAhead]) {
 #pragma unroll
         for (int q = 0; q < kAhead; ++q)
-            r[q] = Row{rFT.get(q), rQ.get(q), rHT.get(q), rR.get(q), ru.get(q), ry.get(q) - rd.get(q)};
+            r[q] = In{rFT.get(q), rQ.get(q), rHT.get(q), rR.get(q), ru.get(q), rd.get(q), ry.get(q)};
         rFT.move(kAhead);
         rQ.move(kAhead);
         rHT.move(kAhead);
@@ -337,13 +505,14 @@ __global__ __launch_bounds__(64) void k_chain_filter_tv(Args a, int pass) {
     // straight-line code for a group: what does not depend on the moments fills the
     // latencies of what does.  Chains enter and end at a group's edge (the last
     // of a sequence aside, which nobody follows); steps beyond the end are dropped.
-    auto use = [&](const Row (&r)[kAhead]) {
+    auto use = [&](const In (&r)[kAhead]) {
         if (k == s && todo) store_state(a.entry, x.c, t, P, m);
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) {
             const bool out = k + q < e && k + q >= s;
-            bool fine = row_ok<NY>(r[q], t);
-            filter_step<NY>(r[q], t, m, P, fine);
+            const Row z{r[q].FT, r[q].Q, r[q].HT, r[q].R, r[q].u, (double)r[q].y - r[q].d};
+            bool fine = row_ok<NY>(z, t);
+            filter_step<NY>(z, t, m, P, fine);
             ok &= fine | !out;
             oP.put(q, sym(P, t), out);
             om.put(q, m, out);
@@ -411,7 +580,8 @@ __global__ __launch_bounds__(64) void k_chain_smoother_tv(Args a, int pass) {
     oP.open(static_cast<const T*>(a.Ps), n2, a.total, kb, kl, at.nn, at.q);
     bool ok = true;
     struct In {
-        double FT, Q, u, m, P;
+        double FT, Q, u;
+        T m, P;
     } g[3][kAhead];
     auto fetch = [&](In (&r)[kAhead]) {
 #pragma unroll
@@ -428,10 +598,11 @@ __global__ __launch_bounds__(64) void k_chain_smoother_tv(Args a, int pass) {
         for (int q = kAhead - 1; q >= 0; --q) {
             double ET, Pp, mp;
             bool fine = true;
-            smoother_gain<NX>(r[q].FT, r[q].Q, r[q].u, r[q].m, r[q].P, t, ET, Pp, mp, fine);
+            const double m = (double)r[q].m, P = (double)r[q].P;
+            smoother_gain<NX>(r[q].FT, r[q].Q, r[q].u, m, P, t, ET, Pp, mp, fine);
             const bool on = k + q < top, out = k + q < e && k >= s;
             double mn = ms, Pn = Ps;
-            smoother_step(ET, Pp, mp, r[q].m, r[q].P, mn, Pn);
+            smoother_step(ET, Pp, mp, m, P, mn, Pn);
             ms = on ? mn : ms;
             Ps = on ? Pn : Ps;
             ok &= fine | !(out && on);
@@ -453,6 +624,471 @@ __global__ __launch_bounds__(64) void k_chain_smoother_tv(Args a, int pass) {
         use(g[1]);
         fetch(g[1]);
         use(g[2]);
+    }
+    if (!ok) a.ctl[0] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// Time-invariant models, one per sequence.  Beyond a sequence's first `head`
+// steps (and before its last, for the smoother) the covariances and gains are
+// the settled ones, and what is left of a step is m_k = A m_{k-1} + B z_k + c
+// (filter: A = Phi, B = K, z = y; smoother, backwards: A = E, B = I - E F, z the
+// filtered mean).  16 steps at a time, z_{4 j + q} as column j of tile q:
+//   S      the mean before steps 0, 4, 8, 12: a chain of four products with A^4,
+//          from the columns' inputs A^3 B z_0 + A^2 B z_1 + A B z_2 + B z_3 + c';
+//   O_q    the means of steps q, 4 + q, 8 + q, 12 + q, O_q = A O_{q-1} + B Z_q + c.
+// 14 products for 16 steps, 8 where only the last is wanted.
+// Chains that start in there run the means alone from half as many steps again
+// as the covariances take to settle (the mean forgets at half their rate, and
+// they settle 2^-60 deep); those whose start would fall into the head start
+// with the sequence.
+// Bound by the slowest head (0.33 us a step of the filter, and as the smoother's
+// tail and head 0.2 and 0.45) beside the rows to write: 8.5 M steps of 1024 CV
+// models, mixed: filter 190 us (143 without the settled rows), smoother 310
+// (257); the general scan, 1225 in all.  Loads are eight groups ahead, and
+// results are written a row a lane: in pieces of 16 bytes the filter took 30 us
+// more.
+// ---------------------------------------------------------------------------
+constexpr int kLong = 16;            // steps of a group
+constexpr int kPace = 4;             // stores in flight of a wave that writes settled rows
+constexpr int kWriters = 512;        // of such waves
+constexpr int kDeep = 8;             // groups whose loads are in flight
+
+__device__ __forceinline__ double pick_of(int j, double a, double b, double c, double d) {
+    const double lo = j & 1 ? b : a, hi = j & 1 ? d : c;
+    return j & 2 ? hi : lo;
+}
+
+struct Affine {
+    double AT, A4T, BT, c;                   // tiles of A^T, (A^4)^T, B^T; c in all columns
+    double BqT[4], c4;                       // of A^{3-q} B; the constant of four steps
+    __device__ __forceinline__ void set(double at, double bt, double c0, const Lane& t) {
+        AT = at;
+        BT = bt;
+        c = c0;
+        const double A = trans(at, t);
+        // (X Y)^T = mm(Y, X^T)
+        const double A2T = mm(A, AT);
+        A4T = mm(trans(A2T, t), A2T);
+        BqT[3] = bt;
+        c4 = c0;
+#pragma unroll
+        for (int q = 2; q >= 0; --q) {
+            BqT[q] = mm(trans(BqT[q + 1], t), AT);
+            c4 = mm(AT, c4, c0);
+        }
+    }
+    // m: the mean before the group (in every column), then the one after it; BACK:
+    // the steps from the last to the first, tiles and columns in reverse
+    template <bool BACK>
+    __device__ __forceinline__ void run(double& m, const double (&z)[4], double (&o)[4], bool rows, const Lane& t) const {
+        double in = c4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) in = mm(BqT[q], z[BACK ? 3 - q : q], in);
+        const double s0 = m, s1 = mm(A4T, s0, col<BACK ? 3 : 0>(in)), s2 = mm(A4T, s1, col<BACK ? 2 : 1>(in)),
+                     s3 = mm(A4T, s2, col<BACK ? 1 : 2>(in));
+        m = mm(A4T, s3, col<BACK ? 0 : 3>(in));
+        if (!rows) return;
+        const int j = BACK ? 3 - t.j : t.j;
+        double x = pick_of(j, s0, s1, s2, s3);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) o[BACK ? 3 - q : q] = x = mm(AT, x, mm(BT, z[BACK ? 3 - q : q], c));
+        o[BACK ? 0 : 3] = pick_of(j, s1, s2, s3, m);
+    }
+};
+
+// column j of the lane's row -> column j - 1 (and 0 -> 3), or the other way
+template <bool UP>
+__device__ __forceinline__ double turn(double x) {
+    constexpr int ctl = UP ? (3 | 0 << 2 | 1 << 4 | 2 << 6) : (1 | 2 << 2 | 3 << 4 | 0 << 6);
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, ctl, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), ctl, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// vectors of 16 rows: tile q has row 4 j + q as column j
+template <typename T>
+__device__ __forceinline__ void open_cols(Rows<T>& r, const T* p, int words, int64_t total, int64_t k0, int64_t k,
+                                          const Lane& t) {
+    r.open(p, words, total, k0, k, t.i < words, 4 * t.j * words + t.i);
+}
+// end of the steps with settled covariances that start at lo + head
+__device__ __forceinline__ int64_t settled_end(int64_t lo, int64_t hi, int tail, bool smoothed) {
+    return smoothed ? lo + ((hi - lo - tail) & -(int64_t)kLong) : hi;
+}
+// The settled covariance in all the rows that hold it: a wave's share is a
+// contiguous range of rows, written 16 bytes a lane (NX = 4).  Waves of their own,
+// behind the chains' in the same launch, each with few stores in flight: the
+// chains' loads and stores queue behind them.  8.5 M steps, FP32, 100 us by
+// themselves; beside the chains they add 165 us if those write them, 100 with
+// stores unpaced, 47 with four in flight.
+template <typename T, int NX, bool SMOOTHED>
+__device__ __forceinline__ void write_settled(const Args& a, int64_t w, int64_t nw, T* dst) {
+    typedef unsigned unit_t __attribute__((ext_vector_type(NX == 4 ? 4 : sizeof(T) / 4)));
+    constexpr int n2 = NX * NX, V = sizeof(unit_t) / sizeof(T), U = n2 / V, L = 64 / U * U;     // units a row, lanes in use
+    const int lane = threadIdx.x & 63, part = lane % U;
+    int64_t r = a.total * w / nw;
+    const int64_t r1 = a.total * (w + 1) / nw;
+    if (r >= r1 || lane >= L) return;
+    int lo = 0, hi = a.B;                             // offsets[lo] <= r < offsets[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (a.offsets[mid] <= r) lo = mid; else hi = mid;
+    }
+    for (int b = lo; r < r1; ++b) {
+        const int64_t s = a.offsets[b], e = a.offsets[b + 1];
+        const int head = a.head[2 * b], tail = a.head[2 * b + 1];
+        const int64_t c0 = max(r, s + head), c1 = min(r1, settled_end(s, e, tail, SMOOTHED));
+        if (c0 < c1) {
+            T v[V];
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                const int q = part * V + i;
+                v[i] = (T)a.model[(int64_t)b * kModel + (SMOOTHED ? 80 : 48) + q / NX * 4 + q % NX];
+            }
+            unit_t x;
+            __builtin_memcpy(&x, v, sizeof x);
+            unit_t* p = reinterpret_cast<unit_t*>(dst + c0 * n2) + lane;
+            const int64_t units = (c1 - c0) * U;
+            int64_t q = lane;
+            for (; q + (kPace / 2 - 1) * L < units; q += kPace / 2 * L) {
+#pragma unroll
+                for (int i = 0; i < kPace / 2; ++i, p += L) __builtin_memcpy(p, &x, sizeof x);
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPace / 2) : "memory");
+            }
+            for (; q < units; q += L, p += L) __builtin_memcpy(p, &x, sizeof x);
+        }
+        r = min(e, r1);
+    }
+}
+
+// the vectors of 16 steps, o_q(i, j) entry i of step 4 j + q: written a row a
+// lane by way of LDS (NX = 4; else as they lie): 256 or 512 consecutive bytes a
+// chain and store, not 16 pieces
+template <typename T, int NX>
+struct OutRows {
+    Rows<T> r;
+    T* st;
+    __device__ __forceinline__ void open(const T* p, int64_t total, int64_t k0, int64_t k, const Lane& t, T* lds) {
+        if constexpr (NX == 4) {
+            r.open(p, NX, total, k0, k, true, NX * (4 * t.i + t.j));
+            st = lds + 64 * t.b;
+        } else {
+            open_cols(r, p, NX, total, k0, k, t);
+        }
+    }
+    // the rows k .. end - 1 of the group
+    __device__ __forceinline__ void put(const double (&o)[4], int k, int end, const Lane& t) const {
+        if constexpr (NX == 4) {
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) st[(4 * t.j + q) * 4 + t.i] = (T)o[q];
+            w16::wave_sync_lds();
+            const int at = (int)(k + 4 * t.i + t.j < end ? r.at : kOutside);
+#pragma unroll
+            for (int h = 0; h < (int)sizeof(T) / 4; ++h) {
+                u32x4 x;
+                __builtin_memcpy(&x, reinterpret_cast<const char*>(st + (4 * t.i + t.j) * 4) + 16 * h, 16);
+                __builtin_amdgcn_raw_buffer_store_b128(x, r.rs, at, 16 * h, 0);
+            }
+            w16::wave_sync_lds();
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) r.put(q, o[q], k + 4 * t.j + q < end);
+        }
+    }
+};
+
+template <typename T, int NX, int NY>
+__global__ __launch_bounds__(64) void k_chain_filter_ti(Args a, int pass, int writers) {
+    __shared__ __align__(16) T stage[256];
+    if (a.ctl[0] == 0) return;
+    const int chains = gridDim.x - writers;           // waves of chains, then of settled rows
+    if ((int)blockIdx.x >= chains)
+        return write_settled<T, NX, false>(a, blockIdx.x - chains, writers, static_cast<T*>(a.P));
+    const Lane t = lane_of();
+    const Chain x = chain_of(a, (int64_t)blockIdx.x * 4 + t.b);
+    const At at = at_of(t, NX, NY);
+    constexpr int n2 = NX * NX;
+    const double* md = a.model + x.b * kModel + 4 * t.i + t.j;
+    const double Pstar = md[48];
+    const int head = a.head[2 * x.b];
+    const int64_t warm = (head + head / 2 + kLong - 1) & -kLong;
+    int64_t k0 = pass ? x.s : x.s - warm;
+    if (pass == 0 && k0 < x.lo + head) k0 = x.lo;
+    bool todo = x.live;
+    double m, P;
+    if (pass == 0) {
+        P = k0 == x.lo ? pick(at.nn, a.P0[x.b * n2 + at.q]) : Pstar;
+        m = t.i < NX ? a.m0[x.b * NX + (t.i < NX ? t.i : 0)] : 0.0;
+    } else {
+        double oP, om;
+        load_state(a.end[0], x.s > x.lo ? x.c - 1 : x.c, t, P, m);
+        load_state(a.entry, x.c, t, oP, om);
+        const bool same = agree(oP, om, P, m, t) || x.s == x.lo;
+        if (same && x.live) {
+            load_state(a.end[0], x.c, t, oP, om);
+            store_state(a.end[1], x.c, t, oP, om);
+        }
+        todo = todo && !same;
+        if (!__any(todo)) return;
+    }
+    const double FT = pick(at.nn, a.F[x.b * n2 + at.ft]), Q = pick(at.nn, a.Q[x.b * n2 + at.q]);
+    const double HT = pick(at.mn, a.H[x.b * (NX * NY) + at.ht]), R = pick(at.mm, a.R[x.b * (NY * NY) + at.r]);
+    const double u = a.u && t.i < NX ? a.u[x.b * NX + t.i] : 0.0, d = a.d && t.i < NY ? a.d[x.b * NY + t.i] : 0.0;
+    Affine f;
+    f.set(md[0], md[16], col<0>(md[32]), t);
+    // chains of a wave need not start in order: the lowest start is the base
+    int64_t kb = k0;
+#pragma unroll
+    for (int s = 4; s < 16; s <<= 1) kb = min(kb, (int64_t)__shfl_xor((long long)kb, s, 64));
+    kb = uniform(kb);
+    int k = (int)(k0 - kb);
+    const int s = (int)(x.s - kb), e = todo ? (int)(x.e - kb) : k, settled = (int)(x.lo + head - kb);
+    Rows<T> ry, oP;
+    open_cols(ry, static_cast<const T*>(a.y), NY, a.total, kb, k0, t);
+    OutRows<T, NX> om;
+    om.open(static_cast<const T*>(a.m), a.total, kb, k0, t, stage);
+    oP.open(static_cast<const T*>(a.P), n2, a.total, kb, k0, at.nn, at.q);
+    bool ok = true;
+    auto fetch = [&](T (&r)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[q] = ry.get(q);
+        ry.move(kLong);
+    };
+    auto begin = [&] {
+        if (k == s && todo) store_state(a.entry, x.c, t, P, m);
+    };
+    auto finish = [&](const double (&o)[4]) {
+        if (__any(k >= s && k < e)) om.put(o, k, k >= s ? e : k, t);
+        k += kLong;
+        om.r.move(kLong);
+        if (k == e && todo) store_state(a.end[pass], x.c, t, P, m);
+    };
+    // heads of sequences: the first groups of chains that start with one
+    if (__any(k < settled && k < e)) {
+        T cur[4], nxt[4];
+        fetch(cur);
+        while (__any(k < settled && k < e)) {
+            fetch(nxt);
+            begin();
+            double z[4] = {(double)cur[0], (double)cur[1], (double)cur[2], (double)cur[3]}, o[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+            for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    bool fine = true;
+                    filter_step<NY>(Row{FT, Q, HT, R, u, col<0>(z[q]) - d}, t, m, P, fine);
+                    P = k >= settled ? Pstar : P;
+                    o[q] = t.j == j ? m : o[q];
+                    const bool put = k >= s && k + 4 * j + q < e;
+                    ok &= fine | !put;
+                    oP.put(q, sym(P, t), put && k < settled);
+                    z[q] = turn<false>(z[q]);
+                }
+                oP.move(4);
+            }
+            finish(o);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cur[q] = nxt[q];
+        }
+        ry.move(-kLong);
+    }
+    P = Pstar;
+    T g[kDeep][4];
+#pragma unroll
+    for (int i = 0; i < kDeep; ++i) fetch(g[i]);
+    while (__any(k < e)) {
+#pragma unroll
+        for (int i = 0; i < kDeep; ++i) {
+            const double y[4] = {(double)g[i][0], (double)g[i][1], (double)g[i][2], (double)g[i][3]};
+            double o[4] = {0.0, 0.0, 0.0, 0.0};
+            begin();
+            f.template run<false>(m, y, o, __any(k >= s && k < e), t);
+            finish(o);
+            fetch(g[i]);
+        }
+    }
+    if (!ok) a.ctl[0] = 0;
+}
+
+template <typename T, int NX>
+__global__ __launch_bounds__(64) void k_chain_smoother_ti(Args a, int pass, int writers) {
+    __shared__ __align__(16) T stage[256];
+    if (a.ctl[0] == 0) return;
+    const int chains = gridDim.x - writers;
+    if ((int)blockIdx.x >= chains)
+        return write_settled<T, NX, true>(a, blockIdx.x - chains, writers, static_cast<T*>(a.Ps));
+    const Lane t = lane_of();
+    const Chain x = chain_of(a, (int64_t)blockIdx.x * 4 + t.b);
+    const At at = at_of(t, NX, 1);
+    constexpr int n2 = NX * NX;
+    const double* md = a.model + x.b * kModel + 4 * t.i + t.j;
+    const double Pstar = md[48], ETs = md[64], Psstar = md[80];
+    const int head = a.head[2 * x.b], tail = a.head[2 * x.b + 1];
+    const int64_t warm = (tail + tail / 2 + kLong - 1) & -kLong;
+    int64_t from = pass ? x.e : x.e + warm;          // the step with known moments
+    if (from > x.hi - 1 - tail && (pass == 0 || x.e == x.hi)) from = x.hi - 1;
+    bool todo = x.live;
+    double ms, Ps;
+    if (pass == 0) {
+        const double Pl = pick(at.nn, (double)static_cast<const T*>(a.P)[from * n2 + at.q]);
+        ms = t.i < NX ? (double)static_cast<const T*>(a.m)[from * NX + t.i] : 0.0;
+        const double Pend = x.hi - x.lo >= head ? Pstar : Pl;
+        Ps = from < x.hi - 1 ? Psstar : Pend;
+        if (x.live && from < x.e) {                   // a sequence's last step
+            if (at.nn) static_cast<T*>(a.Ps)[from * n2 + at.q] = (T)Pend;
+            if (at.n) static_cast<T*>(a.ms)[from * NX + at.v] = (T)ms;
+        }
+    } else {
+        double oP, om;
+        load_state(a.end[0], x.e < x.hi ? x.c + 1 : x.c, t, Ps, ms);
+        load_state(a.entry, x.c, t, oP, om);
+        const bool same = agree(oP, om, Ps, ms, t) || x.e == x.hi;
+        if (same && x.live) {
+            load_state(a.end[0], x.c, t, oP, om);
+            store_state(a.end[1], x.c, t, oP, om);
+        }
+        todo = todo && !same;
+        if (!__any(todo)) return;
+    }
+    const double FT = pick(at.nn, a.F[x.b * n2 + at.ft]), Q = pick(at.nn, a.Q[x.b * n2 + at.q]);
+    const double u = a.u && t.i < NX ? a.u[x.b * NX + t.i] : 0.0;
+    const double Pps = mm(FT, mm(Pstar, FT), Q);      // F P F^T + Q, settled
+    Affine f;
+    {
+        // B = I - E F, c = -E u
+        const double I = t.i == t.j && t.i < NX ? 1.0 : 0.0;
+        f.set(ETs, trans(I - mm(ETs, trans(FT, t)), t), -mm(ETs, u), t);
+    }
+    const int64_t kb = uniform(x.s);                  // of the wave's first chain: the lowest step
+    const int s = (int)(x.s - kb), e = (int)(x.e - kb), top = (int)(from - kb);
+    const int first = (int)(x.lo + head - 1 - kb);    // P has settled from here on
+    const int last = (int)(x.hi - 1 - tail - kb);     // Ps has up to here
+    int k = todo ? s + (top - s + kLong - 1) / kLong * kLong - kLong : s - kLong;       // a group's lowest step
+    const int64_t kl = kb + k;
+    Rows<T> rm, rP, oP;
+    open_cols(rm, static_cast<const T*>(a.m), NX, a.total, kb, kl, t);
+    rP.open(static_cast<const T*>(a.P), n2, a.total, kb, kl, at.nn, at.q);
+    OutRows<T, NX> om;
+    om.open(static_cast<const T*>(a.ms), a.total, kb, kl, t, stage);
+    oP.open(static_cast<const T*>(a.Ps), n2, a.total, kb, kl, at.nn, at.q);
+    bool ok = true;
+    auto fetch = [&](T (&r)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[q] = rm.get(q);
+        rm.move(-kLong);
+    };
+    auto begin = [&] {
+        if (k + kLong == e && todo) store_state(a.entry, x.c, t, Ps, ms);
+    };
+    auto finish = [&](const double (&o)[4]) {
+        const int end = k >= s ? min(e, top) : k;     // rows to write: k .. end - 1
+        if (__any(k < end)) om.put(o, k, end, t);
+        if (k == s && todo) store_state(a.end[pass], x.c, t, Ps, ms);
+        k -= kLong;
+        om.r.move(-kLong);
+    };
+    // the chain's group has rows of the sequence's head or tail
+    auto edge = [&](int kk) { return kk >= s && (kk < first || kk + kLong - 1 > last); };
+    if (todo && k < s) store_state(a.end[pass], x.c, t, Ps, ms);       // a chain of one step, the sequence's last
+    int at_k = k;                                     // where rP and oP stand
+    while (__any(k >= s)) {
+        if (__any(edge(k))) {
+            rP.move(k - at_k);
+            oP.move(k - at_k);
+            T cur[4], nxt[4], Pc[kLong], Pn[kLong];
+            auto fetch_P = [&](T (&r)[kLong], int kk) {       // of the head, all else is known
+                if (__any(kk >= s && kk < first)) {
+#pragma unroll
+                    for (int q = 0; q < kLong; ++q) r[q] = rP.get(q);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < kLong; ++q) r[q] = T(0);
+                }
+                rP.move(-kLong);
+            };
+            fetch(cur);
+            fetch_P(Pc, k);
+            while (__any(edge(k))) {
+                fetch(nxt);
+                fetch_P(Pn, k - kLong);
+                begin();
+                const int end = k >= s ? min(e, top) : k;
+                const bool mine = edge(k);
+                const bool varies = __any(k >= s && k < first);
+                double z[4] = {(double)cur[0], (double)cur[1], (double)cur[2], (double)cur[3]}, o[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int j = 3; j >= 0; --j) {
+                    double ET[4], Pp[4], mp[4], mq[4], P[4];
+#pragma unroll
+                    for (int q = 3; q >= 0; --q) {
+                        mq[q] = col<3>(z[q]);
+                        z[q] = turn<true>(z[q]);
+                        P[q] = k + 4 * j + q >= first ? Pstar : (double)Pc[4 * j + q];
+                    }
+                    if (varies) {                     // four gains, independent of each other
+#pragma unroll
+                        for (int q = 3; q >= 0; --q) {
+                            bool fine = true;
+                            smoother_gain<NX>(FT, Q, u, mq[q], P[q], t, ET[q], Pp[q], mp[q], fine);
+                            ok &= fine | !(k + 4 * j + q < end);
+                        }
+                    } else {
+#pragma unroll
+                        for (int q = 3; q >= 0; --q) {
+                            ET[q] = ETs;
+                            Pp[q] = Pps;
+                            mp[q] = mm(FT, mq[q], u);
+                        }
+                    }
+#pragma unroll
+                    for (int q = 3; q >= 0; --q) {
+                        const int kq = k + 4 * j + q;
+                        const bool on = kq < top;
+                        double mn = ms, Psn = Ps;
+                        smoother_step(ET[q], Pp[q], mp[q], mq[q], P[q], mn, Psn);
+                        ms = on ? mn : ms;
+                        Ps = on ? (kq >= first && kq <= last ? Psstar : Psn) : Ps;
+                        o[q] = t.j == j ? ms : o[q];
+                        oP.put(4 * j + q, sym(Ps, t), kq < end && mine);
+                    }
+                }
+                oP.move(-kLong);
+                finish(o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) cur[q] = nxt[q];
+#pragma unroll
+                for (int q = 0; q < kLong; ++q) Pc[q] = Pn[q];
+            }
+            rm.move(kLong);                           // (one group was fetched ahead)
+            rP.move(kLong);
+            at_k = k;
+        } else {
+            Ps = Psstar;
+            T g[kDeep][4];
+#pragma unroll
+            for (int i = 0; i < kDeep; ++i) fetch(g[i]);
+            bool more = true;
+            while (more) {
+#pragma unroll
+                for (int i = 0; i < kDeep; ++i) {
+                    const double m[4] = {(double)g[i][0], (double)g[i][1], (double)g[i][2], (double)g[i][3]};
+                    double o[4] = {0.0, 0.0, 0.0, 0.0};
+                    begin();
+                    f.template run<true>(ms, m, o, __any(k >= s && k < min(e, top)), t);
+                    finish(o);
+                    if (!__any(k >= s) || __any(edge(k))) {
+                        more = false;
+                        break;
+                    }
+                    fetch(g[i]);
+                }
+            }
+            // back to the group after the last one taken
+            rm.move(kLong * kDeep - kLong);
+        }
     }
     if (!ok) a.ctl[0] = 0;
 }
@@ -484,56 +1120,80 @@ void timed(const char* name, hipStream_t s, F&& f) {
 }
 
 template <typename T, int NX, int NY>
-hipError_t run(const Args& a, hipStream_t s) {
-    const dim3 grid((unsigned)((a.max_chains + 3) / 4)), wave(64);
-    timed("k_chain_setup", s, [&] { hipLaunchKernelGGL(k_chain_setup, dim3(1), wave, 0, s, a); });
+hipError_t run(const Args& a, bool tv, hipStream_t s) {
+    const int writers = kWriters;
+    const dim3 grid((unsigned)((a.max_chains + 3) / 4)), more(grid.x + writers), wave(64);
+    timed("k_chain_setup", s, [&] { hipLaunchKernelGGL(k_chain_setup, dim3(1), dim3(a.offsets ? 1024 : 64), 0, s, a); });
+    if (!tv)
+        timed("k_chain_models", s,
+              [&] { hipLaunchKernelGGL((k_chain_models<NX, NY>), dim3((a.B + 3) / 4), wave, 0, s, a); });
     for (int pass = 0; pass < 2; ++pass)
-        timed(pass ? "k_chain_filter_again" : "k_chain_filter", s,
-              [&] { hipLaunchKernelGGL((k_chain_filter_tv<T, NY>), grid, wave, 0, s, a, pass); });
+        timed(pass ? "k_chain_filter_again" : "k_chain_filter", s, [&] {
+            if (tv) hipLaunchKernelGGL((k_chain_filter_tv<T, NY>), grid, wave, 0, s, a, pass);
+            else hipLaunchKernelGGL((k_chain_filter_ti<T, NX, NY>), pass ? grid : more, wave, 0, s, a, pass, pass ? 0 : writers);
+        });
     timed("k_chain_check", s, [&] { hipLaunchKernelGGL((k_chain_check<false>), grid, wave, 0, s, a); });
     if (a.smooth) {
         for (int pass = 0; pass < 2; ++pass)
-            timed(pass ? "k_chain_smoother_again" : "k_chain_smoother", s,
-                  [&] { hipLaunchKernelGGL((k_chain_smoother_tv<T, NX>), grid, wave, 0, s, a, pass); });
+            timed(pass ? "k_chain_smoother_again" : "k_chain_smoother", s, [&] {
+                if (tv) hipLaunchKernelGGL((k_chain_smoother_tv<T, NX>), grid, wave, 0, s, a, pass);
+                else hipLaunchKernelGGL((k_chain_smoother_ti<T, NX>), pass ? grid : more, wave, 0, s, a, pass, pass ? 0 : writers);
+            });
         timed("k_chain_check", s, [&] { hipLaunchKernelGGL((k_chain_check<true>), grid, wave, 0, s, a); });
     }
     return hipGetLastError();
 }
 
 template <typename T, int NX>
-hipError_t run_ny(const Args& a, hipStream_t s) {
+hipError_t run_ny(const Args& a, bool tv, hipStream_t s) {
     switch (a.ny) {
-        case 1: return run<T, NX, 1>(a, s);
-        case 2: return run<T, NX, 2>(a, s);
-        case 3: return run<T, NX, 3>(a, s);
-        default: return run<T, NX, 4>(a, s);
+        case 1: return run<T, NX, 1>(a, tv, s);
+        case 2: return run<T, NX, 2>(a, tv, s);
+        case 3: return run<T, NX, 3>(a, tv, s);
+        default: return run<T, NX, 4>(a, tv, s);
     }
 }
 template <typename T>
-hipError_t run_nx(const Args& a, hipStream_t s) {
-    return a.nx == 3 ? run_ny<T, 3>(a, s) : run_ny<T, 4>(a, s);
+hipError_t run_nx(const Args& a, bool tv, hipStream_t s) {
+    return a.nx == 3 ? run_ny<T, 3>(a, tv, s) : run_ny<T, 4>(a, tv, s);
 }
 
 }  // namespace
 
-// Filter + smoother, general scan and chains, us:       FP64        mixed (FP32 elements)
-//   nx = 4, ny = 2, 2^18 steps                        371, 249      273, 259
-//                   2^19                              677, 305      531, 312
-//   nx = 3, ny = 1, 2^18                              256, 235      192, 241
-//                   2^19                              543, 280      379, 286
-//   nx = 4, ny = 4, 2^18                              459, 331      360, 369
-//   nx = 2, ny = 1, 2^20                              551, 934      465, 860
+// Time-varying models.  Filter + smoother, general scan and chains, us:
+//                                                   FP64            mixed (FP32 elements)
+//   nx = 4, ny = 2, 2^18 steps                      371, 249        273, 259
+//                   2^19                            677, 305        531, 312
+//   nx = 3, ny = 1, 2^18                            256, 235        192, 241
+//                   2^19                            543, 280        379, 286
+//   nx = 4, ny = 4, 2^18                            459, 331        360, 369
+//   nx = 2, ny = 1, 2^20                            551, 934        465, 860
 // (the chains' time hardly depends on nx, the general scan's does).  Packed
 // sequences: long enough on average that most chains are full ones.
-bool applies(int nx, int ny, int32_t B, int64_t total, bool mixed) {
-    return nx >= 3 && nx <= 4 && ny <= 4 && total >= (mixed ? 1 << 19 : 1 << 18) && total / B >= 512;
+// A model per sequence (nx = 4, ny = 2, CV models): the head and the tail of a
+// sequence cost as much as about 1500 of its other steps, and a bundle with a
+// model that settles too late goes back to the scan after 35 us, so from well
+// behind the break-even on:
+//   64 sequences, 533 k steps                       301, 254        208, 239
+//                 the filter alone                  158, 108        115, 107
+//   300,          628 k                             313, 361        216, 369
+//   300,          2.46 M                            769, 415        463, 349
+//                 the filter alone                  359, 162        246, 134
+//   1024,         2.05 M                            561, 514        391, 455
+//   1024,         8.30 M                            2047, 871       1249, 568
+bool applies(int nx, int ny, int32_t B, int64_t total, bool mixed, bool tv, bool smooth) {
+    if (nx < 3 || nx > 4 || ny > 4) return false;
+    if (tv) return total >= (mixed ? 1 << 19 : 1 << 18) && total / B >= 512;
+    return total - 1536 * (int64_t)B >= (int64_t)(mixed ? 2 : 1) * (smooth ? 3 << 18 : 3 << 17);
 }
 
-bool layout(Args& a, char* base, size_t bytes) {
-    // CV models of all step sizes in use agree to rounding after 100 to 180 steps
+bool layout(Args& a, char* base, size_t bytes, bool tv) {
+    // time-varying: CV models of all step sizes in use agree to rounding after 100 to
+    // 180 steps; else the setup knows
     a.warm = 192;
-    a.l = (a.total + 4095) / 4096;                    // (at least 64)
-    a.l = (a.l + kAhead - 1) / kAhead * kAhead;       // chains start and end with a group of steps
+    a.l = tv ? (a.total + 4095) / 4096 : std::max<int64_t>(64, (a.total + 12287) / 12288);
+    const int group = tv ? kAhead : kLong;            // chains start and end with a group of steps
+    a.l = (a.l + group - 1) / group * group;
     a.max_chains = (a.total + a.l - 1) / a.l + (a.offsets ? a.B : 0);
     char* p = base;
     auto take = [&](int64_t words) {
@@ -542,14 +1202,17 @@ bool layout(Args& a, char* base, size_t bytes) {
         return q;
     };
     a.first = reinterpret_cast<int64_t*>(take(a.B + 1));
+    a.sequence = a.offsets ? reinterpret_cast<int*>(take((a.max_chains + 1) / 2)) : nullptr;
+    a.model = tv ? nullptr : take((int64_t)a.B * kModel);
+    a.head = tv ? nullptr : reinterpret_cast<int*>(take(a.B));
     a.entry = take(a.max_chains * kState);
     a.end[0] = take(a.max_chains * kState);
     a.end[1] = take(a.max_chains * kState);
     return (size_t)(p - base) <= bytes;
 }
 
-hipError_t launch(const Args& a, bool mixed, hipStream_t s) {
-    return mixed ? run_nx<float>(a, s) : run_nx<double>(a, s);
+hipError_t launch(const Args& a, bool mixed, bool tv, hipStream_t s) {
+    return mixed ? run_nx<float>(a, tv, s) : run_nx<double>(a, tv, s);
 }
 
 }  // namespace chains

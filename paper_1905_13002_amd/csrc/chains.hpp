@@ -1,5 +1,5 @@
 // chains.hpp -- filter and smoother by overlapped chains: models that change at
-// every step (nx, ny <= 4).
+// every step, and packed sequences with a model each (nx, ny <= 4).
 //
 // A filter that follows its state forgets where it started.  The sequences are
 // cut into chains of l steps; every chain runs the sequential recursion from
@@ -10,7 +10,9 @@
 // not agree run once more from the predecessor's end; if one still differs, or
 // a factorisation failed, the flag ctl[0] is cleared and the general scan
 // kernels, which follow in the stream and return at once otherwise, do the
-// work.  The smoother does the same backwards.
+// work.  The smoother does the same backwards.  With one time-invariant model per
+// sequence, covariances that have settled are not run again: there a chain is the
+// means alone.
 #pragma once
 #include "pks_internal.h"
 
@@ -18,6 +20,7 @@ namespace pks {
 namespace chains {
 
 constexpr int kState = 32;           // doubles of a chain's moments: tiles of P and of the mean
+constexpr int kModel = 96;           // doubles of a time-invariant model's settled values: six tiles
 
 struct Args {
     int nx, ny, B;
@@ -26,19 +29,22 @@ struct Args {
     int each;                    // one prior per sequence
     int64_t total;
     const int64_t* offsets;      // device [B+1]; nullptr: one sequence
-    const double *F, *u, *Q, *H, *d, *R, *m0, *P0;     // a row of F, u, Q, H, d, R per step
+    const double *F, *u, *Q, *H, *d, *R, *m0, *P0;     // one row per step (time-varying) or per sequence
     const void* y;
     void *m, *P, *ms, *Ps;
     int* status;
     int* ctl;                    // [0] 1: this path has done the work
     int64_t l, warm, max_chains;
     int64_t* first;              // [B+1] chains of the sequences before
+    int* sequence;               // [chains] a chain's sequence (packed sequences)
+    double* model;               // [B][kModel] settled values (time-invariant models)
+    int* head;                   // [B][2] steps after which P and Ps have settled, in 16 (0: they have not)
     double *entry, *end[2];      // [chains][kState] moments that a chain entered and ended with
 };
 
-bool applies(int nx, int ny, int32_t B, int64_t total, bool mixed);
-bool layout(Args& a, char* base, size_t bytes);
-hipError_t launch(const Args& a, bool mixed, hipStream_t s);
+bool applies(int nx, int ny, int32_t B, int64_t total, bool mixed, bool tv, bool smooth);
+bool layout(Args& a, char* base, size_t bytes, bool tv);
+hipError_t launch(const Args& a, bool mixed, bool tv, hipStream_t s);
 
 }  // namespace chains
 }  // namespace pks

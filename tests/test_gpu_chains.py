@@ -1,4 +1,5 @@
-"""Time-varying models by overlapped chains (csrc/chains.hip): the path taken
+"""Time-varying models, and packed sequences with a model each, by overlapped
+chains (csrc/chains.hip): the path taken
 (a word of the workspace's status block), every step against the oracle at the
 parity bars, for every size that takes the path, lengths around the edges of
 chains and groups of steps, packed sequences shorter and longer than a chain,
@@ -117,3 +118,65 @@ def test_failing_factorisation_is_flagged(pks):
     assert ctl == 0
     ok, first = pks.read_numeric_status(ws)
     assert not ok and first == 0
+
+
+# ---------------------------------------------------------------------------
+# one time-invariant model per sequence
+# ---------------------------------------------------------------------------
+def each(nx, ny, lengths, seed, model=None):
+    rng = np.random.default_rng(seed)
+    def draw():                                  # forgets fast enough: noise in every direction, all of it seen
+        m = wl.random_small_model(nx, ny, rng)
+        return wl.Model(0.8 * m.F, m.Q, m.H, m.R, m.m0, m.P0, m.u, m.d)
+    models = [(model or draw)() for _ in lengths]
+    row = lambda f: None if getattr(models[0], f) is None else np.stack([getattr(m, f) for m in models])
+    packed = wl.Model(*(row(f) for f in ("F", "Q", "H", "R", "m0", "P0", "u", "d")))
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    return models, packed, offsets, rng.standard_normal((int(offsets[-1]), ny))
+
+
+def run_each(pks, packed, offsets, y, precision):
+    dm, yd, off = pks.to_device(packed, per_sequence=True), dev(y, precision), torch.as_tensor(offsets).cuda()
+    plan = pks.Plan(dm, yd, off, precision)
+    for _ in range(3):
+        out = plan.launch()
+        torch.cuda.synchronize()
+    return out, int(plan.ws[:256].cpu().numpy().view(np.int32)[CTL]), dm, yd, off
+
+
+LENGTHS = [1, 15, 0, 16, 17, 300, 1041, 2, 4097, 131072, 33001, 70000]
+
+
+@pytest.mark.parametrize("nx,ny,precision", [(3, 1, "fp64"), (3, 3, "mixed"), (4, 1, "mixed"), (4, 2, "fp64"),
+                                             (4, 3, "fp64"), (4, 4, "mixed")])
+def test_each_its_model(pks, nx, ny, precision):
+    """Sequences of one step, of less than a head, of many chains, an empty one."""
+    lengths = LENGTHS + [600003 if precision == "fp64" else 1400003]
+    models, packed, offsets, y = each(nx, ny, lengths, seed=100 * nx + ny)
+    out, ctl, dm, yd, off = run_each(pks, packed, offsets, y, precision)
+    assert ctl == 1
+    yy = y if precision == "fp64" else y.astype(np.float32).astype(np.float64)
+    for b, (s, e) in enumerate(zip(offsets[:-1], offsets[1:])):
+        if s == e:
+            continue
+        mo = models[b]
+        ref = oracle.kf_rts(mo.F, mo.Q, mo.H, mo.R, mo.m0, mo.P0, yy[s:e], u=mo.u, d=mo.d)
+        for k, v in zip(("m", "P", "ms", "Ps"), out):
+            err = wl.max_rel_err(v[s:e].double().cpu().numpy(), ref[k], "rms" if precision == "mixed" else "none")
+            assert err <= TOL[precision], (b, k, err)
+    m, P = pks.filter_batched(dm, off, yd, precision)
+    assert torch.equal(m, out[0]) and torch.equal(P, out[1])
+
+
+@pytest.mark.parametrize("q", [0.0, 1e-9])
+def test_each_its_model_that_settles_late(pks, q):
+    """One model of a constant (nearly constant) state among them: the general scan."""
+    lengths = [200000, 3000, 300000, 400000]
+    models, packed, offsets, y = each(4, 2, lengths, seed=9)
+    packed.F[1], packed.Q[1] = np.eye(4), q * np.eye(4)
+    out, ctl, _, _, _ = run_each(pks, packed, offsets, y, "fp64")
+    assert ctl == 0
+    mo, (s, e) = models[3], offsets[3:5]
+    ref = oracle.kf_rts(mo.F, mo.Q, mo.H, mo.R, mo.m0, mo.P0, y[s:e], u=mo.u, d=mo.d)
+    for k, v in zip(("m", "P", "ms", "Ps"), out):
+        assert wl.max_rel_err(v[s:e].cpu().numpy(), ref[k]) <= TOL["fp64"], k
