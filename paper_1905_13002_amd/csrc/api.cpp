@@ -40,7 +40,6 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
-constexpr int kMinEpt = 4;          // smallest elements-per-thread any configuration uses
 constexpr int kMaxDim = 64;
 
 constexpr int64_t kMaxStepsTv = 0x7fffffff;   // time-varying: one constant block per step, indexed by int32
@@ -88,7 +87,7 @@ WsLayout ws_layout(int nx, int ny, int64_t total, int32_t nmodels, pks_precision
     L.model_fail = o; o = align256(o + sizeof(int32_t) * (size_t)nmodels);
     L.top_flags = o; o = align256(o + sizeof(int32_t) * (size_t)(1 + kTopMaxWorkgroups));
     // small-state scan: level 0 over steps, level 1 over level-0 wave aggregates
-    const int64_t waves0 = round_up(std::max<int64_t>(1, ceil_div(total, 64 * kMinEpt)), 4);
+    const int64_t waves0 = round_up(std::max<int64_t>(1, ceil_div(small_threads(nx, total), 64)), 4);
     const int64_t thr0 = waves0 * 64;
     const int64_t waves1 = round_up(std::max<int64_t>(1, ceil_div(waves0, 64)), 4);   // >= 1 item per thread
     const int64_t thr1 = waves1 * 64;
@@ -210,7 +209,7 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
     const bool small = small_supported(model.nx);
     const bool mixed = prec == PKS_MIXED_FP32;
     TileConfig cfg = forced ? *forced : tuned_config(model.nx, model.ny, B, total, prec);
-    if (cfg.ept < kMinEpt) cfg.ept = kMinEpt;
+    if (cfg.ept < 1) cfg.ept = 1;
     if (!small_supported(model.nx)) cfg.ept1 = 0;   // the large-state path reads only cfg.blocks
     // Time-invariant models with settling covariances: the setup decides on the
     // device; the general kernels follow and return at once when it has done

@@ -153,7 +153,7 @@ __host__ __device__ __forceinline__ int64_t const_offset(const ScanArgs& a, int 
 
 // Tile configuration chosen for a launch.
 struct TileConfig {
-    int ept = 16;    // elements per thread, level 0 (4, 8, 16)
+    int ept = 16;    // elements per thread, level 0 (1, 2, 4, 8, 16)
     int ept1 = 0;    // elements per thread, level 1 (aggregates); 0 = no level 1
     int blocks = 0;  // large states (nx >= 5): blocks of the time axis (Section III-C's
                   // block elements); 0 = the default count
@@ -181,6 +181,7 @@ hipError_t launch_precompute(int nx, int ny, int32_t nmodels, const pks_model& m
 // passes: 1 = filter, 2 = smoother, 3 = both (fused where possible)
 hipError_t launch_small(ScanArgs a, bool mixed, int passes, hipStream_t s);
 TileConfig small_default_config(int nx, int64_t total, bool mixed);
+int64_t small_threads(int nx, int64_t total);      // level-0 threads to allow for
 
 // Debug mode (pks_set_debug_poison, or the environment variable
 // PKS_DEBUG_POISON set to anything but 0): every call first fills the

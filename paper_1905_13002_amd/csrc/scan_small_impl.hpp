@@ -1148,6 +1148,10 @@ hipError_t run_m(ScanArgs a, int passes, hipStream_t s) {
 
 template <int N, typename R, bool SEG>
 hipError_t dispatch_ept(ScanArgs a, int passes, hipStream_t s) {
+    if constexpr (N >= 3) {                       // (small_default_config)
+        if (a.ept == 1) return run_m<N, R, 1, SEG>(a, passes, s);
+        if (a.ept == 2) return run_m<N, R, 2, SEG>(a, passes, s);
+    }
     switch (a.ept) {
         case 4: return run_m<N, R, 4, SEG>(a, passes, s);
         case 8: return run_m<N, R, 8, SEG>(a, passes, s);
