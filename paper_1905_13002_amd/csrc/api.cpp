@@ -216,14 +216,16 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
     // the work.
     hipError_t e;
     const int* skip = nullptr;
-    if ((passes & 1) && !tv && !model.per_sequence && steady::applies(model.nx, model.ny, B, total, mixed)) {
+    if (((passes & 1) || model.nx > 16) && !tv && !model.per_sequence &&
+        steady::applies(model.nx, model.ny, B, total, mixed)) {
         char* base = static_cast<char*>(ws);
         steady::Args t{};
         t.nx = model.nx; t.ny = model.ny; t.B = B;
         t.total = total;
         t.offsets = offsets;
         t.smooth = (passes & 2) != 0;
-        t.reset = 1;
+        t.given = passes == 2;
+        t.reset = passes & 1;
         t.F = model.F; t.u = model.u; t.Q = model.Q; t.H = model.H; t.d = model.d; t.R = model.R;
         t.m0 = model.m0; t.P0 = model.P0;
         t.y = y; t.m = m; t.P = P; t.ms = ms; t.Ps = Ps;

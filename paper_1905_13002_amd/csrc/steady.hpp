@@ -20,6 +20,9 @@
 // Phi^L, E^L beyond the head.  A model that does not settle within the table's
 // N steps leaves the flag ctl[0] at zero, and the general scan kernels, which
 // follow in the stream and return at once when the flag is set, do the work.
+// The smoother alone (nx > 16) compares every filtered covariance that it is
+// given with the table's, in the storage type: they are those of the filter
+// here, or the general kernels take the call.
 #pragma once
 #include "pks_internal.h"
 
@@ -35,6 +38,7 @@ struct Args {
     int N;                       // longest head the tables hold (a power of two)
     int pL;                      // log2 of the steps per chain
     int smooth;                  // filter + smoother (else the filter alone)
+    int given;                   // the smoother alone, of filtered moments that the call has
     int reset;
     int64_t total;
     const int64_t* offsets;      // device [B+1]; nullptr: one sequence

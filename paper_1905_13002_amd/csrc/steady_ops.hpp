@@ -107,8 +107,9 @@ template <typename R> struct Unit<R, 16> { using T = unsigned __attribute__((ext
 template <typename R> struct Unit<R, 8> { using T = unsigned __attribute__((ext_vector_type(2))); };
 template <typename R> struct Unit<R, 4> { using T = unsigned; };
 
-template <typename R, int BYTES, bool SMOOTHED>
-__device__ __forceinline__ void write_rows_u(const Args& a, int nh, int64_t wg, int64_t nwg, R* lds) {
+// CHECK: compares the rows that are there instead; true if one differs
+template <typename R, int BYTES, bool SMOOTHED, bool CHECK>
+__device__ __forceinline__ bool write_rows_u(const Args& a, int nh, int64_t wg, int64_t nwg, R* lds) {
     using UT = typename Unit<R, BYTES>::T;
     constexpr int V = BYTES / (int)sizeof(R);
     const int n = a.nx, n2 = n * n;
@@ -122,7 +123,8 @@ __device__ __forceinline__ void write_rows_u(const Args& a, int nh, int64_t wg, 
     int64_t row = r0 + threadIdx.x / upr;
     int off = threadIdx.x % upr;
     const int srow = S / upr, soff = S % upr;
-    if (row >= r1) return;
+    bool differs = false;
+    if (row >= r1) return false;
     int b = a.offsets ? seq_holding(a.offsets, a.B, row) : 0;
     SeqR q = seq_of(a, b);
     UT* out = reinterpret_cast<UT*>(dst);
@@ -149,7 +151,16 @@ __device__ __forceinline__ void write_rows_u(const Args& a, int nh, int64_t wg, 
         } else {
             __builtin_memcpy(&v, lds + off * V, BYTES);
         }
-        if (mine) __builtin_nontemporal_store(v, out + row * upr + off);
+        if constexpr (CHECK) {
+            const UT x = out[row * upr + off];
+            unsigned vw[BYTES / 4], xw[BYTES / 4];
+            __builtin_memcpy(vw, &v, BYTES);
+            __builtin_memcpy(xw, &x, BYTES);
+#pragma unroll
+            for (int i = 0; i < BYTES / 4; ++i) differs |= vw[i] != xw[i];
+        } else if (mine) {
+            __builtin_nontemporal_store(v, out + row * upr + off);
+        }
         row += srow;
         off += soff;
         if (off >= upr) {
@@ -157,11 +168,17 @@ __device__ __forceinline__ void write_rows_u(const Args& a, int nh, int64_t wg, 
             ++row;
         }
     }
+    return differs;
 }
 template <typename R, bool SMOOTHED>
 __device__ __forceinline__ void write_rows(const Args& a, int nh, int64_t wg, int64_t nwg, R* lds) {
-    if ((a.nx & 1) == 0) write_rows_u<R, 16, SMOOTHED>(a, nh, wg, nwg, lds);
-    else write_rows_u<R, sizeof(R), SMOOTHED>(a, nh, wg, nwg, lds);
+    if ((a.nx & 1) == 0) write_rows_u<R, 16, SMOOTHED, false>(a, nh, wg, nwg, lds);
+    else write_rows_u<R, sizeof(R), SMOOTHED, false>(a, nh, wg, nwg, lds);
+}
+template <typename R>
+__device__ __forceinline__ bool rows_differ(const Args& a, int nh, int64_t wg, int64_t nwg, R* lds) {
+    return (a.nx & 1) == 0 ? write_rows_u<R, 16, false, true>(a, nh, wg, nwg, lds)
+                           : write_rows_u<R, sizeof(R), false, true>(a, nh, wg, nwg, lds);
 }
 
 // column of a tile <-> vector of n in memory

@@ -152,3 +152,39 @@ def test_nan_and_failed_models(pks):
     ws = pks.workspace(6, 2, 9000)
     m, _ = pks.filter(pks.to_device(bad), torch.as_tensor(y).cuda(), "fp64", ws=ws)
     assert pks.read_numeric_status(ws) == (False, 0) and torch.isnan(m).all()
+
+
+# ---------------------------------------------------------------------------
+# the smoother alone (nx > 16) of covariances that are the filter's own
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("nx,ny,lengths,precision", [(17, 5, [9000], "fp64"), (24, 10, [3000, 1, 700, 5001], "mixed"),
+                                                     (33, 20, [8193], "mixed"), (64, 32, [2000, 6400], "fp64")])
+def test_smoother_alone(pks, nx, ny, lengths, precision):
+    rng = np.random.default_rng(nx)
+    model = wl.random_stable_model(nx, ny, rng, radius=0.9, with_offsets=True)
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    T = int(off[-1])
+    y = rng.standard_normal((T, ny))
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    dm, yd, offd = pks.to_device(model), torch.as_tensor(y).to("cuda", dt), torch.as_tensor(off).cuda()
+    ws = pks.workspace(nx, ny, T, len(lengths), precision)
+    word = lambda: int(ws[:256].cpu().numpy().view(np.int32)[CTL])
+    m, P = pks.filter_batched(dm, offd, yd, precision, ws=ws)
+    ms, Ps = pks.smooth_batched(dm, offd, m, P, precision, ws=ws)
+    torch.cuda.synchronize()
+    assert word() > 0
+    yy = y if precision == "fp64" else y.astype(np.float32).astype(np.float64)
+    for s, e in zip(off[:-1], off[1:]):
+        ref = oracle.kf_rts(model.F, model.Q, model.H, model.R, model.m0, model.P0, yy[s:e], u=model.u, d=model.d)
+        for k, v in zip(("ms", "Ps"), (ms, Ps)):
+            err = wl.max_rel_err(v[s:e].double().cpu().numpy(), ref[k], "rms" if precision == "mixed" else "none")
+            assert err <= TOL[precision], (s, k, err)
+    # covariances that are not the filter's, by one bit of one entry early or late: the general kernels
+    for row in (1, T - 400):
+        Q = P.clone()
+        Q[row, 1, 1] *= 1 + 2 * torch.finfo(dt).eps
+        m2, P2 = pks.smooth_batched(dm, offd, m, Q, precision, ws=ws)
+        torch.cuda.synchronize()
+        assert word() == 0
+        assert (P2 - Ps).abs().max() <= TOL[precision] * Ps.abs().max()
+        assert (m2 - ms).abs().max() <= TOL[precision] * ms.abs().max()
