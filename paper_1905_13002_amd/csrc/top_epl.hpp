@@ -9,11 +9,11 @@
 // and down-sweep kernels) costs about 1,600 dependent vector instructions per
 // filtering combine; with 16 lanes per element a 4 x 4 product is one
 // v_mfma_f64_4x4x4f64 and the (I + C_i J_j) solve a 4-step Gauss-Jordan
-// elimination with lane exchanges.
+// elimination whose rows and columns move by products and quad permutes.
 //
 // Grid: up to kTopMaxWg workgroups of 256 threads (one wave per SIMD: a
-// combine is about 2,400 cycles of mostly issued instructions, so waves that
-// share a SIMD slow each other down), 16 groups of 16 lanes each.  Group G of
+// combine is mostly issued instructions, so waves that share a SIMD slow each
+// other down), 16 groups of 16 lanes each.  Group G of
 // workgroup w folds E consecutive items, the 16 groups are scanned with a
 // Kogge-Stone pattern through LDS, the workgroup publishes its aggregate (a
 // flag per workgroup, release/acquire at device scope) and then combines the
@@ -58,11 +58,18 @@ __device__ __forceinline__ double mtm(double x, double y) {
     return __builtin_amdgcn_mfma_f64_4x4x4f64(x, y, 0.0, 0, 0, 0);
 }
 __device__ __forceinline__ double from_lane(double v, int src) { return __shfl(v, src, 64); }
-__device__ __forceinline__ double transposed(double v, const Lanes& L) {
-    return from_lane(v, 16 * L.c + L.g4 + L.r);
-}
-__device__ __forceinline__ double sym(double v, const Lanes& L) { return 0.5 * (v + transposed(v, L)); }
 __device__ __forceinline__ double eye(const Lanes& L) { return L.r == L.c ? 1.0 : 0.0; }
+// (a product with ones and zeros: exact, and a quarter of a lane permute's latency)
+__device__ __forceinline__ double transposed(double v, const Lanes& L) { return mtm(v, eye(L)); }
+__device__ __forceinline__ double sym(double v, const Lanes& L) { return 0.5 * (v + transposed(v, L)); }
+// entry (r, p) in the lanes of row r
+template <int p>
+__device__ __forceinline__ double column(double v) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, 0x55 * p, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), 0x55 * p, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 // every entry of the group's matrix is exactly zero
 __device__ __forceinline__ bool group_zero(double v, const Lanes& L) {
     const unsigned long long nz = __ballot(v != 0.0);
@@ -78,7 +85,7 @@ __device__ __forceinline__ double pick4(const double (&v)[4], int i) {
 // permutes; gfx950's cross-row permlane swaps (three per 32-bit half to bring
 // all four rows to every lane) measured slower here: 2,550 against 2,100
 // cycles per inverse.
-__device__ __forceinline__ double inverse4(double x, const Lanes& L) {
+__device__ __noinline__ double inverse4_pivoted(double x, const Lanes& L) {
     double v = eye(L);
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -109,6 +116,28 @@ __device__ __forceinline__ double inverse4(double x, const Lanes& L) {
     return v;
 }
 
+// one pivot on the diagonal, in place: the pivot row comes from a product with
+// ones and zeros, the pivot column along the quads
+template <int p>
+__device__ __forceinline__ double pivot_in_place(double x, const Lanes& L) {
+    const double row = mtm(L.r == p ? 1.0 : 0.0, x), col = column<p>(x);
+    const double rp = rcp64(column<p>(row));
+    const double rr = L.c == p ? rp : row * rp;
+    const double v = fma(-col, rr, L.c == p ? 0.0 : x);
+    return L.r == p ? rr : v;
+}
+// The inverse of x, xt its transpose.  The matrices here are I + C J with C and J
+// positive semidefinite, for which pivots on the diagonal nearly always do (600
+// cycles): one Newton step, and the pivoted elimination where the residual before
+// it is not small.  k_filter_top, with the transposes by products: 26 to 10 us at
+// nx = 2, T = 100003 (391 waves), 23 to 14 at nx = 4, 624 k steps in 300 sequences.
+__device__ __forceinline__ double inverse4(double x, double xt, const Lanes& L) {
+    const double v = pivot_in_place<3>(pivot_in_place<2>(pivot_in_place<1>(pivot_in_place<0>(x, L), L), L), L);
+    const double res = eye(L) - mtm(xt, v);
+    if (__any(!(fabs(res) <= 1e-8))) return inverse4_pivoted(x, L);
+    return v + mtm(transposed(v, L), res);
+}
+
 // ---------------------------------------------------------------------------
 // elements in the 16-lane layout
 // ---------------------------------------------------------------------------
@@ -131,7 +160,7 @@ __device__ __forceinline__ void ident(ES& e, const Lanes& L) {
 // so mtm(W, Y) = M^-1 Y.  With K = M^-1 A_i, A_i^T M^-T = K^T.
 template <bool G>
 __device__ __forceinline__ void epl_fcombine(const EF& ei, const EF& ej, EF& o, const Lanes& L) {
-    const double W = inverse4(mtm(ej.J, ei.C) + eye(L), L);   // C, J symmetric: J_j^T C_i = J_j C_i
+    const double W = inverse4(mtm(ej.J, ei.C) + eye(L), mtm(ei.C, ej.J) + eye(L), L);   // C, J symmetric: J_j^T C_i = J_j C_i
     const double K = mtm(W, ei.A);
     const double x2 = mtm(W, ei.b + mtm(ei.C, ej.eta));        // M^-1 (b_i + C_i eta_j)
     const double Z = mtm(W, ei.C);                             // M^-1 C_i (symmetric)
@@ -155,7 +184,7 @@ __device__ __forceinline__ void epl_fcombine(const EF& ei, const EF& ej, EF& o, 
 // x <- x (x) j for a prefix x whose A is zero (moments only)
 template <bool G>
 __device__ __forceinline__ void epl_fcarry(EM& x, const EF& ej, const Lanes& L) {
-    const double W = inverse4(mtm(ej.J, x.P) + eye(L), L);
+    const double W = inverse4(mtm(ej.J, x.P) + eye(L), mtm(x.P, ej.J) + eye(L), L);
     const double x2 = mtm(W, x.m + mtm(x.P, ej.eta));
     const double Z = mtm(W, x.P);
     double m = mtm(ej.At, x2) + ej.b;

@@ -58,3 +58,26 @@ def test_workspace_grows_with_the_length(pks, nx, precision):
     dt = torch.float64 if precision == "fp64" else torch.float32
     pks.filter_smooth(pks.to_device(model), torch.zeros((32768, 2), dtype=dt, device="cuda"), precision, ws=ws)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (2, 1), (2, 2), (3, 2), (4, 2), (4, 4)])
+def test_strongly_correlated_noise(pks, nx, ny):
+    """I + C J far from symmetric: its leading entries can be small or negative,
+    where the top level's elimination (pivots on the diagonal) has to notice."""
+    for seed in range(6):
+        rng = np.random.default_rng([nx, ny, seed])
+        B, D = rng.standard_normal((nx, nx)), 10.0 ** rng.uniform(-1.5, 1.5, size=nx)
+        F = rng.standard_normal((nx, nx))
+        F *= 0.95 / np.abs(np.linalg.eigvals(F)).max()
+        Q = B @ np.diag(D) @ B.T
+        H, Rr = rng.standard_normal((ny, nx)), rng.standard_normal((ny, ny))
+        model = wl.Model(F, 0.5 * (Q + Q.T) + 1e-3 * np.eye(nx), H, Rr @ Rr.T + 0.05 * np.eye(ny),
+                         rng.standard_normal(nx), np.eye(nx))
+        T = 20011
+        y = 10.0 * rng.standard_normal((T, ny))
+        out = pks.filter_smooth(pks.to_device(model), torch.as_tensor(y).cuda(), "fp64")
+        torch.cuda.synchronize()
+        ref = oracle.kf_rts(model.F, model.Q, model.H, model.R, model.m0, model.P0, y)
+        for k, v in zip(("m", "P", "ms", "Ps"), out):
+            e = wl.max_rel_err(v.cpu().numpy(), ref[k], "rms")
+            assert e <= TOL["fp64"], (seed, k, e)
