@@ -223,7 +223,7 @@ __device__ __forceinline__ void gain_offset(const Eng<NT>& e, const Args& a, con
 
 // The smoother alone.  Whether it is worth the setup (0.3 ms at nx = 24): the last
 // two filtered covariances of the longest sequence are the same (ctl[3] = 0).
-// 40 sequences of 100 to 2000 steps, nx = 24, mixed: 0.65 ms, of which the
+// 40 sequences of 100 to 2000 steps, nx = 24, mixed: 0.5 ms, of which the
 // comparison below is 30 us; by the general kernels 4.0 ms.
 template <typename R>
 __global__ __launch_bounds__(256) void k_stl_probe(Args a) {
@@ -516,31 +516,35 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_head_fill(Args a, const do
         e.st(a.tHead + (int64_t)(k - 1) * n2, Ps, n, n);
     }
 }
-// a sequence shorter than 2 n: its head folded from its own last covariances
+// a sequence shorter than 2 n: its head folded from its own last covariances, a
+// workgroup for the rows of each run, which the elements of the runs behind it
+// reach in a step each (step by step, one workgroup a sequence: 204 us for 40
+// sequences of nx = 24, a head of 128; so 55)
 template <typename R, int NT>
 __global__ __launch_bounds__(64 * NT * NT) void k_stl_short_head(Args a) {
     extern __shared__ __align__(16) double lds[];
-    const int nh = a.ctl[0];
-    if (nh == 0) return;
+    const int nh = a.ctl[0], run = blockIdx.y;
+    if (nh == 0 || run >= nh / kRun) return;
     const SeqR q = seq_of(a, blockIdx.x);
     const int64_t len = q.end - q.start;
     if (len >= 2 * nh || len < 1) return;
+    int k = (int)(len < nh ? len : nh) - 1;          // the step that Ps is of
+    const int last = k / kRun;
+    if (run > last) return;
     const Eng<NT> e(lds, a);
     const int n = a.nx, n2 = n * n;
     R* out = static_cast<R*>(a.Ps) + q.start * n2;
-    int64_t k;
-    f64x4 Ps;
-    if (len >= nh) {
-        k = nh - 1;
-        Ps = e.ld(a.tTail + (len - nh) * n2, n, n);
-    } else {
-        k = len - 1;
-        Ps = e.ld(a.tP + k * n2, n, n);
-        e.st(out + k * n2, Ps, n, n);
+    f64x4 Ps = e.ld(len < nh ? a.tP + (int64_t)k * n2 : a.tTail + (len - nh) * n2, n, n);
+    auto back = [&](const double* E, const double* L) { Ps = e.ele(e.ldt(E, n, n), Ps, e.ld(L, n, n)); };
+    if (run < last) {
+        for (; k >= last * kRun; --k) back(a.tE + (int64_t)(k - 1) * n2, a.tL + (int64_t)(k - 1) * n2);
+        for (int r = last - 1; r > run; --r) back(a.runE + (int64_t)r * n2, a.runL + (int64_t)r * n2);
+        k = run * kRun + kRun - 1;
     }
-    for (; k > 0; --k) {
-        Ps = e.ele(e.ldt(a.tE + (k - 1) * n2, n, n), Ps, e.ld(a.tL + (k - 1) * n2, n, n));
-        e.st(out + (k - 1) * n2, Ps, n, n);
+    if (run < last || len < nh) e.st(out + (int64_t)k * n2, Ps, n, n);
+    for (; k > run * kRun; --k) {
+        back(a.tE + (int64_t)(k - 1) * n2, a.tL + (int64_t)(k - 1) * n2);
+        e.st(out + (int64_t)(k - 1) * n2, Ps, n, n);
     }
 }
 
@@ -994,7 +998,7 @@ hipError_t run(const Args& a, hipStream_t s) {
         hipLaunchKernelGGL((k_stl_head_fill<NT>), dim3(runs), wide, eng, s, a, sE, sL);
         prof_end(s);
         prof_begin("k_stl_short_head", s);
-        if (a.B > 1) hipLaunchKernelGGL((k_stl_short_head<R, NT>), dim3(a.B), wide, eng, s, a);
+        if (a.B > 1) hipLaunchKernelGGL((k_stl_short_head<R, NT>), dim3(a.B, runs), wide, eng, s, a);
         prof_end(s);
     }
     const GridL g{(int64_t)((a.B + 15) / 16) * runs, a.max_blocks};
