@@ -375,33 +375,33 @@ __global__ __launch_bounds__(kThreads) void k_w16_filter_reduce(W16Args w) {
 }
 
 // out[i] = in[i - d] (x) in[i] (i >= d), else in[i]
-__global__ __launch_bounds__(kThreads) void k_w16_filter_ks(W16Args w, const double* in, double* out, int64_t d) {
+__global__ __launch_bounds__(kThreads) void k_w16_filter_ks(W16Args w, const double* in, double* out, int64_t d, int radix) {
     if (skipped(w.s)) return;
     __shared__ double st[kStage];
     const int64_t i = blockIdx.x;
-    const double* rj = in + (size_t)i * kFRec;
     double* ro = out + (size_t)i * kFRec;
-    const f64x4 Aj = get_tile(rj + kFA), Cj = get_tile(rj + kFC), Jj = get_tile(rj + kFJ);
-    const f64x4 bj = load_vec(rj + kFb, 16), etaj = load_vec(rj + kFeta, 16);
-    FE e;
-    if (i < d) {
-        e.A = Aj; e.C = Cj; e.J = Jj; e.b = bj; e.eta = etaj;
-    } else {
-        const int n = w.s.nx;
-        const double* ri = in + (size_t)(i - d) * kFRec;
-        e.A = get_tile(ri + kFA);
-        e.C = get_tile(ri + kFC);
-        e.J = get_tile(ri + kFJ);
-        e.b = load_vec(ri + kFb, 16);
-        e.eta = load_vec(ri + kFeta, 16);
-        const f64x4 I = eye();
-        fcombine(e, tr(Aj, st), bj, Cj, etaj, Jj, I, st, n, w.pivot_always != 0);
-        if (w.s.offsets && all_zero(Aj)) {
+    auto load = [&](int64_t at) {
+        const double* r = in + (size_t)at * kFRec;
+        FE e;
+        e.A = get_tile(r + kFA);
+        e.C = get_tile(r + kFC);
+        e.J = get_tile(r + kFJ);
+        e.b = load_vec(r + kFb, 16);
+        e.eta = load_vec(r + kFeta, 16);
+        return e;
+    };
+    FE e = load(i);
+#pragma unroll 1
+    for (int s = 1; s < radix && i >= s * d; ++s) {
+        const FE j = e;
+        e = load(i - s * d);
+        fcombine(e, tr(j.A, st), j.b, j.C, j.eta, j.J, eye(), st, w.s.nx, w.pivot_always != 0);
+        if (w.s.offsets && all_zero(j.A)) {
             // the right operand starts a sequence: its A, b, C pass through
             // (exactly what A_j = 0 gives, without 0 * NaN from the left)
-            e.A = Aj;
-            e.b = bj;
-            e.C = Cj;
+            e.A = j.A;
+            e.b = j.b;
+            e.C = j.C;
         }
     }
     put_tile(ro + kFA, e.A);
@@ -561,23 +561,25 @@ __global__ __launch_bounds__(kThreads) void k_w16_smoother_reduce(W16Args w) {
 }
 
 // out[i] = in[i] (x) in[i + d] (i + d < nb), else in[i]
-__global__ __launch_bounds__(kThreads) void k_w16_smoother_ks(W16Args w, const double* in, double* out, int64_t d) {
+__global__ __launch_bounds__(kThreads) void k_w16_smoother_ks(W16Args w, const double* in, double* out, int64_t d, int radix) {
     if (skipped(w.s)) return;
     __shared__ double st[kStage];
     const int64_t i = blockIdx.x;
-    const double* ri = in + (size_t)i * kSRec;
     double* ro = out + (size_t)i * kSRec;
-    const f64x4 Ei = get_tile(ri + kSE), Li = get_tile(ri + kSL), gi = load_vec(ri + kSg, 16);
-    f64x4 E, g, L;
-    // the left operand ending a sequence (E = 0) passes through
-    if (i + d >= w.nblocks || (w.s.offsets && all_zero(Ei))) {
-        E = Ei; g = gi; L = Li;
-    } else {
-        const double* rj = in + (size_t)(i + d) * kSRec;
-        E = get_tile(rj + kSE);
-        L = get_tile(rj + kSL);
-        g = load_vec(rj + kSg, 16);
-        sfold(E, g, L, tr(Ei, st), gi, Li, st);
+    int s = radix - 1;
+    while (i + s * d >= w.nblocks) --s;
+    const double* r = in + (size_t)(i + s * d) * kSRec;
+    f64x4 E = get_tile(r + kSE), L = get_tile(r + kSL), g = load_vec(r + kSg, 16);
+#pragma unroll 1
+    while (--s >= 0) {
+        r = in + (size_t)(i + s * d) * kSRec;
+        const f64x4 Ei = get_tile(r + kSE), Li = get_tile(r + kSL), gi = load_vec(r + kSg, 16);
+        // the left operand ending a sequence (E = 0) passes through
+        if (w.s.offsets && all_zero(Ei)) {
+            E = Ei; g = gi; L = Li;
+        } else {
+            sfold(E, g, L, tr(Ei, st), gi, Li, st);
+        }
     }
     put_tile(ro + kSE, E);
     put_tile(ro + kSL, L);
@@ -906,6 +908,10 @@ template <typename R>
 hipError_t run(W16Args w, bool smoother, hipStream_t s) {
     const dim3 grid((unsigned)w.nblocks), block(kThreads);
     int cur = 0;
+    // Levels of two are the faster scan.  Behind the settled covariances, which
+    // nearly always have done the work, it is the launches that count (2.2 us
+    // each that returns at once): levels of four, half as many.
+    const int radix = w.s.skip ? 4 : 2;
     if (!smoother) {
         prof_begin("k_w16_filter_reduce", s);
         switch (w.s.ny < 16 ? slices(w.s.ny) : 5) {
@@ -916,9 +922,9 @@ hipError_t run(W16Args w, bool smoother, hipStream_t s) {
             default: hipLaunchKernelGGL((k_w16_filter_reduce<R, 4, false>), grid, block, 0, s, w); break;   // ny = 16
         }
         prof_end(s);
-        for (int64_t d = 1; d < w.nblocks; d <<= 1) {
+        for (int64_t d = 1; d < w.nblocks; d *= radix) {
             prof_begin("k_w16_filter_ks", s);
-            hipLaunchKernelGGL(k_w16_filter_ks, grid, block, 0, s, w, w.agg[cur], w.agg[cur ^ 1], d);
+            hipLaunchKernelGGL(k_w16_filter_ks, grid, block, 0, s, w, w.agg[cur], w.agg[cur ^ 1], d, radix);
             prof_end(s);
             cur ^= 1;
         }
@@ -936,9 +942,9 @@ hipError_t run(W16Args w, bool smoother, hipStream_t s) {
         prof_begin("k_w16_smoother_reduce", s);
         hipLaunchKernelGGL(k_w16_smoother_reduce<R>, grid, block, 0, s, w);
         prof_end(s);
-        for (int64_t d = 1; d < w.nblocks; d <<= 1) {
+        for (int64_t d = 1; d < w.nblocks; d *= radix) {
             prof_begin("k_w16_smoother_ks", s);
-            hipLaunchKernelGGL(k_w16_smoother_ks, grid, block, 0, s, w, w.agg[cur], w.agg[cur ^ 1], d);
+            hipLaunchKernelGGL(k_w16_smoother_ks, grid, block, 0, s, w, w.agg[cur], w.agg[cur ^ 1], d, radix);
             prof_end(s);
             cur ^= 1;
         }

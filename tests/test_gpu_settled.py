@@ -188,3 +188,18 @@ def test_smoother_alone(pks, nx, ny, lengths, precision):
         assert word() == 0
         assert (P2 - Ps).abs().max() <= TOL[precision] * Ps.abs().max()
         assert (m2 - ms).abs().max() <= TOL[precision] * ms.abs().max()
+
+
+@pytest.mark.parametrize("nx,lengths", [(6, [8192]), (16, [10007]), (9, [3001, 1, 2000, 0, 6000]), (16, [1024] * 9)])
+def test_general_scan_behind_a_failed_attempt(pks, nx, lengths):
+    """4 < nx <= 16, covariances that do not settle: scan levels of four."""
+    rng = np.random.default_rng(nx)
+    model = wl.random_stable_model(nx, nx // 2, rng)
+    model = wl.Model(np.eye(nx), 1e-4 * np.eye(nx), model.H, model.R, model.m0, model.P0)
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    y = rng.standard_normal((int(off[-1]), nx // 2))
+    out, head = run(pks, model, y, "fp64", off if len(lengths) > 1 else None)
+    assert head == 0
+    for s, e in zip(off[:-1], off[1:]):
+        if s < e:
+            against_oracle({k: v[s:e] for k, v in out.items()}, model, y[s:e], "fp64")
