@@ -85,7 +85,7 @@ __device__ __forceinline__ double pick4(const double (&v)[4], int i) {
 // permutes; gfx950's cross-row permlane swaps (three per 32-bit half to bring
 // all four rows to every lane) measured slower here: 2,550 against 2,100
 // cycles per inverse.
-__device__ __noinline__ double inverse4_pivoted(double x, const Lanes& L) {
+__device__ __forceinline__ double inverse4_pivoted(double x, const Lanes& L) {
     double v = eye(L);
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -134,7 +134,7 @@ __device__ __forceinline__ double pivot_in_place(double x, const Lanes& L) {
 __device__ __forceinline__ double inverse4(double x, double xt, const Lanes& L) {
     const double v = pivot_in_place<3>(pivot_in_place<2>(pivot_in_place<1>(pivot_in_place<0>(x, L), L), L), L);
     const double res = eye(L) - mtm(xt, v);
-    if (__any(!(fabs(res) <= 1e-8))) return inverse4_pivoted(x, L);
+    if (__builtin_expect(__any(!(fabs(res) <= 1e-8)), 0)) return inverse4_pivoted(x, L);      // (behind the kernel, not in its way)
     return v + mtm(transposed(v, L), res);
 }
 
