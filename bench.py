@@ -83,7 +83,26 @@ def kernel_model(nx, ny, rs, tv=False):
     }
     if tv:
         out["k_precompute"] = dict(bytes=rows, flops=pre_flops)
+    # settled covariances: the affine recursions of the means, and the rows of
+    # the covariances, written by other waves of the same launches
+    n2 = nx * nx
+    mean_f, mean_s = 2 * n2 + 2 * nx * ny, 4 * n2
+    for p in ("k_st_", "k_stl_"):
+        out[p + "filter_reduce"] = dict(bytes=(ny + n2) * rs, flops=mean_f)
+        out[p + "filter_down"] = dict(bytes=(ny + 2 * nx) * rs, flops=mean_f + mean_s)
+        out[p + "smoother_down"] = dict(bytes=(2 * nx + n2) * rs, flops=mean_s)
+    # overlapped chains: the sequential recursions (the warm-up not counted)
+    kf, rts = recursion_flops(nx, ny)
+    out["k_chain_filter"] = dict(bytes=ny * rs + mom + (rows if tv else 0), flops=kf)
+    out["k_chain_smoother"] = dict(bytes=2 * mom + ((2 * n2 + nx) * 8 if tv else 0), flops=rts)
     return out
+
+
+def recursion_flops(nx, ny):
+    """One step of the sequential Kalman filter and of the RTS smoother."""
+    n, q = nx, ny
+    kf = 4 * n ** 3 + 2 * n * n + 4 * n * n * q + 2 * n * q * q + q ** 3 / 3 + 4 * n * q
+    return kf, n ** 3 / 3 + 6 * n ** 3 + 4 * n * n
 
 
 def ll_kernel_model(nx, ny, rs):
@@ -97,7 +116,10 @@ def ll_kernel_model(nx, ny, rs):
 
 
 KERNEL_SOURCES = ["paper_1905_13002_amd/csrc/small_ops.hpp", "paper_1905_13002_amd/csrc/scan_small_impl.hpp",
-                  "paper_1905_13002_amd/csrc/top_epl.hpp", "paper_1905_13002_amd/csrc/precompute.hip"]
+                  "paper_1905_13002_amd/csrc/top_epl.hpp", "paper_1905_13002_amd/csrc/precompute.hip",
+                  "paper_1905_13002_amd/csrc/tile16.hpp", "paper_1905_13002_amd/csrc/steady_ops.hpp",
+                  "paper_1905_13002_amd/csrc/steady.hip", "paper_1905_13002_amd/csrc/steady_large.hip",
+                  "paper_1905_13002_amd/csrc/chains.hip"]
 
 
 def sources_sha():
@@ -565,6 +587,12 @@ def main():
             bytes_step += (2 * nx * nx + nx + ny * nx + ny + ny * ny) * 8
         flops_step = (f["f_full"] + f["f_carry"] + 2 * f["f_elem"] + 2 * f["s_elem"] + f["s_full"]
                       + f["s_carry"])
+        prof = results[prec]["prof"]
+        took = max(prof, key=lambda k: prof[k][0] / max(1, prof[k][1]))
+        if took.startswith(("k_st_", "k_stl_")):       # settled covariances: the means, forwards and backwards
+            flops_step = 2 * (2 * nx * nx + 2 * nx * ny + 4 * nx * nx)
+        elif took.startswith("k_chain_"):
+            flops_step = sum(recursion_flops(nx, ny))
         peak_f = FP64_PEAK_TFLOPS if (prec == "fp64" or f64_mixed) else FP32_PEAK_TFLOPS
         t_mem = bytes_step * T / (HBM_PEAK_GBS * 1e9)
         t_alu = flops_step * T / (peak_f * 1e12)
