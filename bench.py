@@ -191,7 +191,7 @@ def summarize_profiles(base, workload_name):
     import sqlite3
 
     def short(n):
-        n = n.replace("pks::(anonymous namespace)::", "").replace("pks::", "")
+        n = re.sub(r"pks::(\w+::)?(\(anonymous namespace\)::)?", "", n)
         m = re.match(r"void (\w+<[^>]*>)", n)
         return m.group(1) if m else n
 
@@ -287,7 +287,7 @@ def summarize_counters(base, wid):
     import sqlite3
 
     def short(n):
-        n = n.replace("pks::(anonymous namespace)::", "").replace("pks::", "").replace("lg::", "").replace("w16::", "")
+        n = re.sub(r"pks::(\w+::)?(\(anonymous namespace\)::)?", "", n)
         m = re.match(r"void (\w+<[^>]*>)", n)
         return m.group(1) if m else n
 
@@ -363,7 +363,7 @@ def summarize_trace(base, wid, op="filter_smooth"):
     cur = sqlite3.connect(os.path.join(base, db[0])).cursor()
     rows = []
     for n, calls, tot, avg in cur.execute("select name, total_calls, total_duration, average from top_kernels"):
-        n = n.replace("pks::(anonymous namespace)::", "").replace("pks::lg::", "").replace("pks::w16::", "").replace("pks::", "")
+        n = re.sub(r"pks::(\w+::)?(\(anonymous namespace\)::)?", "", n)
         m = re.match(r"void (\w+<[^>]*>)", n)
         n = m.group(1) if m else n
         if n.startswith("k_"):
