@@ -265,11 +265,14 @@ __device__ __forceinline__ void store_state(double* p, int64_t c, const Lane& t,
 }
 
 // ---------------------------------------------------------------------------
-// The flags, and the chains of every packed sequence.  (A chain's wave reads its
-// sequence from a table: a search would be ten loads in a row.)
+// The flags, and the chains of every packed sequence.  A chain's wave reads its
+// sequence from a table (a search would be ten loads in a row), which a wave a
+// sequence fills: two sequences of 800 k steps with a model each, 209 us in all,
+// 347 with a thread a sequence.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_chain_setup(Args a) {
-    __shared__ int64_t part[16];
+    __shared__ int64_t part[16], starts[1024];
+    __shared__ int counts[1024];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (tid == 0) {
         if (a.reset || a.status[1] != kStatusMagic) {
@@ -296,12 +299,14 @@ __global__ __launch_bounds__(1024) void k_chain_setup(Args a) {
             if (i < w) ahead += part[i];
             before += part[i];
         }
+        if (b < a.B) a.first[b] = ahead + inc - own;
+        starts[tid] = ahead + inc - own;
+        counts[tid] = (int)own;
         __syncthreads();
-        if (b < a.B) {
-            const int64_t c0 = ahead + inc - own;
-            a.first[b] = c0;
-            for (int64_t c = c0; c < c0 + own; ++c) a.sequence[c] = b;
-        }
+        const int n = min(1024, a.B - b0);
+        for (int i = w; i < n; i += 16)              // a wave a sequence
+            for (int c = lane; c < counts[i]; c += 64) a.sequence[starts[i] + c] = b0 + i;
+        __syncthreads();
     }
     if (tid == 0) a.first[a.B] = before;
 }
