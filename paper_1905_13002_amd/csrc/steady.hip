@@ -918,9 +918,11 @@ hipError_t run_kx(const Args& a, hipStream_t s) {
 
 // Sizes alone decide.  The setup is a chain of latencies (nx = 4: 55 us, nx = 16:
 // 100 us) whatever the length, the general scan's arithmetic grows with T nx^3:
-//   nx = 4: T = 2^17 121 us general, 105 here (FP64), 103 and 107 (mixed; its
-//           general kernels multiply in FP32); T = 2^18 141 / 117, 122 / 114
-//   nx = 3: T = 2^17 94 / 93 (FP64), 2^18 110 / 101 (mixed)
+//   nx = 4: FP64  T = 98304 105 us general, 104 here; 2^17 114, 105; 2^18 135, 119
+//           mixed T = 196608 103, 112; 2^18 114, 116; 393216 146, 126 (its general
+//           kernels multiply in FP32): a size between its line and 2^18 gives up 9 us
+//   nx = 3: FP64  T = 196608 104, 96; 2^18 129, 102
+//           mixed T = 393216 115, 114; 2^19 143, 124
 //   nx <= 2: 123 general, 153 here at T = 2^20
 //   nx = 6: T = 20011 354 / 166; nx = 16: T = 10000 553 / 250
 // and the mean length of packed sequences has to hold a head and a tail.
