@@ -472,8 +472,10 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_down(HmmArgs a, const doubl
 // of its block element) from kWarm steps before it, started from the uniform
 // distribution, and the distribution it entered with is compared with the one
 // its predecessor ended with: block 0 starts from the prior, so where every
-// block entered with its predecessor's end (each entry to kSame of itself)
-// every block has the recursion's own values.  Blocks that did not are run
+// block entered with its predecessor's end (each entry to kSame of itself, the
+// smallest ones too: the metric is that of ratios, and evidence that turns brings
+// any weight back; a state with no weight has none in both) every block has the
+// recursion's own values.  Blocks that did not are run
 // again from the predecessor's end, kRepairs times; if one still differs (a
 // chain that does not forget: a permutation, say) the flag stays clear and the
 // block-element scan above does the work.  The smoother runs the same way
@@ -490,7 +492,6 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_down(HmmArgs a, const doubl
 // ---------------------------------------------------------------------------
 constexpr int kWarm = 448, kRepairs = 3, kAhead = 4;
 constexpr double kSame = 1.4210854715202004e-14;      // 2^-46
-constexpr double kNothing = 1e-300;                   // entries below it on both sides are not compared
 
 struct OverArgs {
     HmmArgs h;
@@ -646,8 +647,7 @@ struct MatVec {
 
 // the wave's distribution x equals y, each entry to kSame of itself
 __device__ __forceinline__ bool same_dist(double x, double y, bool live) {
-    const bool off = live && !(fabs(x - y) <= kSame * y) && !(x < kNothing && y < kNothing);
-    return !__any(off);
+    return !__any(live && !(fabs(x - y) <= kSame * y));
 }
 
 // alpha <- exp(L - M), logp <- M = max over the states: formed once here, read

@@ -1,0 +1,57 @@
+"""What the shortcut paths (settled covariances, overlapped chains, overlapped
+discrete-state blocks) may accept: inputs built so that a looser rule would wave
+a wrong result through.  Either the path has the recursion's values, or its flag
+is clear and the general scan's are there."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1905_13002_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+TOL = {"fp64": 1e-9, "mixed": 1e-4}
+CTL = 16          # word of the status block: nonzero if the path has done the work
+
+
+@pytest.fixture(scope="module")
+def pks():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_13002_amd import pks as mod
+    return mod
+
+
+# ---------------------------------------------------------------------------
+# discrete states
+# ---------------------------------------------------------------------------
+def hmm(pks, Pi, p0, L):
+    ws = pks.hmm_workspace(len(p0), len(L))
+    out = pks.hmm_filter_smooth(pks.hmm_to_device(Pi, p0), torch.as_tensor(L).cuda(), ws=ws)
+    torch.cuda.synchronize()
+    return [v.cpu().numpy() for v in out], [int(v) for v in ws[-256:].cpu().numpy().view(np.int32)[:2]]
+
+
+def hmm_check(Pi, p0, L, out):
+    ref = oracle.hmm_fb(Pi, p0, L)
+    cum, mag = np.cumsum(ref["ll"]), np.cumsum(np.abs(ref["ll"]))
+    assert np.max(np.abs(out[0] - ref["alpha"])) <= 1e-9
+    assert np.max(np.abs(out[1] - cum) / np.maximum(1.0, mag)) <= 1e-9
+    assert np.max(np.abs(out[2] - ref["gamma"])) <= 1e-9
+
+
+@pytest.mark.parametrize("rate,turn", [(1.545, 69.0), (1.6, 70.5)])
+def test_impossible_state_stays_impossible(pks, rate, turn):
+    """Two states that never change, the second one impossible.  A block that starts
+    from the uniform distribution has brought its weight down to 1e-301 (1e-311)
+    by its first step; the last block (64 steps) starts with ten steps of evidence that
+    bring it back up."""
+    T = 1 << 16
+    L = np.zeros((T, 2))
+    L[:, 1] = -rate
+    L[T - 64:T - 54] = [-turn, 0.0]
+    L[T - 54:] = 0.0
+    Pi, p0 = np.eye(2), np.array([1.0, 0.0])
+    out, _ = hmm(pks, Pi, p0, L)
+    hmm_check(Pi, p0, L, out)
+    assert np.all(out[0][:, 0] == 1.0) and np.all(out[2][:, 0] == 1.0)
