@@ -492,6 +492,9 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_down(HmmArgs a, const doubl
 // ---------------------------------------------------------------------------
 constexpr int kWarm = 448, kRepairs = 3, kAhead = 4;
 constexpr double kSame = 1.4210854715202004e-14;      // 2^-46
+// Sums and predictions below the normal range: the reciprocal overflows where the
+// quotient it stands for does not.  Such a block is not accepted.
+constexpr double kNormal = 2.2250738585072014e-308;
 
 struct OverArgs {
     HmmArgs h;
@@ -744,7 +747,7 @@ __global__ __launch_bounds__(64) void k_hmm_filter_over(OverArgs o, int pass) {
     double lp = 0.0, raw[kAhead], lh[kAhead], M[kAhead], r = 1.0;
     const bool want = a.logp != nullptr;
     double Mr = 0.0;
-    bool bad = false;        // a step of the block has no weight: the scan's business
+    bool bad = false;        // a step of the block has no weight, or too little of it: the scan's business
     auto fetch = [&](int64_t kk, double (&v)[kAhead]) {
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) v[j] = (FIRST ? a.alpha : a.L)[(kk + j < e ? kk + j : e - 1) * K + col];
@@ -782,7 +785,7 @@ __global__ __launch_bounds__(64) void k_hmm_filter_over(OverArgs o, int pass) {
             al = y[0] * (w[j] * r);
             const double c = all_sum(al) * (KV / 64.0);
             if ((lane & (kAhead - 1)) == j) cs = c;
-            bad |= k + j < e && !(c > 0.0);
+            bad |= k + j < e && !(c >= kNormal);
             r = recip(c);
             av[j] = al * r;
         }
@@ -808,6 +811,12 @@ __global__ __launch_bounds__(64) void k_hmm_filter_over(OverArgs o, int pass) {
     }
     out[b * KV + x] = al * r;
     if (lane == 0) o.blog[b] = bad ? NAN : lp;
+}
+
+// 1 / pred (zero where no state leads there); a NaN, which no comparison lets
+// pass, in place of what may not be finite
+__device__ __forceinline__ double recip_pred(double x) {
+    return x >= kNormal ? recip(x) : (x > 0.0 ? NAN : 0.0);
 }
 
 // gamma_k <- 1 / pred_{k+1} (zero where no state leads there), pred_{k+1} =
@@ -839,7 +848,7 @@ __global__ __launch_bounds__(64) void k_hmm_pred(OverArgs o) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 if (k + 4 * v + lk < a.T && 16 * t + li < K)
-                    a.gamma[(k + 4 * v + lk) * K + 16 * t + li] = D[t][v] > 0.0 ? recip(D[t][v]) : 0.0;
+                    a.gamma[(k + 4 * v + lk) * K + 16 * t + li] = recip_pred(D[t][v]);
     }
 }
 
@@ -945,8 +954,7 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_over(OverArgs o, int pass) 
             if constexpr (FIRST) {
                 ip[j] = u[j];
             } else {
-                const double r = recip(ip[j]);
-                ip[j] = live && ip[j] > 0.0 ? r : 0.0;
+                ip[j] = live ? recip_pred(ip[j]) : 0.0;
             }
         }
     };
@@ -992,6 +1000,8 @@ __global__ __launch_bounds__(64) void k_hmm_over_check(OverArgs o) {
     const int64_t b = blockIdx.x, p = FILTER ? b - 1 : b + 1;
     if (!FILTER && o.need && *o.need == 0) return;
     if (FILTER && lane == 0 && !(fabs(o.blog[b]) < INFINITY)) atomicAdd(&o.ctl[2], 1);
+    // (the first block's end is compared with nothing)
+    if (!FILTER && b == 0 && __any(!(fabs(o.end[kRepairs & 1][x]) < INFINITY)) && lane == 0) atomicAdd(&o.ctl[3], 1);
     if (p < 0 || p >= o.nblk) return;
     if (!same_dist(o.entry[b * KV + x], o.end[kRepairs & 1][p * KV + x], x < o.h.K) && lane == 0)
         atomicAdd(&o.ctl[FILTER ? 2 : 3], 1);

@@ -55,3 +55,32 @@ def test_impossible_state_stays_impossible(pks, rate, turn):
     out, _ = hmm(pks, Pi, p0, L)
     hmm_check(Pi, p0, L, out)
     assert np.all(out[0][:, 0] == 1.0) and np.all(out[2][:, 0] == 1.0)
+
+
+@pytest.mark.parametrize("gap", [712.0, 720.0, 740.0])
+def test_subnormal_predictions(pks, gap):
+    """A banded chain whose first step all but excludes the second state: the
+    prediction of the third is subnormal (1 / it is not finite at the larger gaps)."""
+    T = 1 << 16
+    Pi = np.array([[0.9, 0.1, 0.0], [0.1, 0.8, 0.1], [0.0, 0.1, 0.9]])
+    L = np.random.default_rng(2).normal(size=(T, 3))
+    L[0] = [0.0, -gap, -2000.0]
+    p0 = np.array([1.0, 0.0, 0.0])
+    out, _ = hmm(pks, Pi, p0, L)
+    assert np.isfinite(out[2]).all()
+    hmm_check(Pi, p0, L, out)
+
+
+def test_subnormal_last_step(pks):
+    """The last step's weight is subnormal: the state that explains it was excluded before."""
+    T = 1 << 16
+    Pi = np.array([[0.9, 0.1, 0.0], [0.1, 0.9, 0.0], [0.0, 0.0, 1.0]])
+    L = np.random.default_rng(3).normal(size=(T, 3))
+    L[:, 2] = -np.inf
+    L[-1] = [-712.0, -713.0, 0.0]
+    p0 = np.full(3, 1.0 / 3.0)
+    out, _ = hmm(pks, Pi, p0, L)
+    assert all(np.isfinite(v).all() for v in out)
+    # the weights exp(-712), exp(-713) are subnormal: 48 and 47 bits
+    ref = oracle.hmm_fb(Pi, p0, L)
+    assert np.max(np.abs(out[0] - ref["alpha"])) <= 1e-9 and np.max(np.abs(out[2] - ref["gamma"])) <= 1e-9
