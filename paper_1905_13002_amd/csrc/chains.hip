@@ -112,10 +112,14 @@ __device__ __forceinline__ double inv_general(double x, const Lane& t, bool& ok)
     if constexpr (N > 3) x = pivot<3>(x, t, ok);
     return x;
 }
-// sum of the squares of a tile, on every lane of the chain
-__device__ __forceinline__ double sumsq(double x, const Lane& t) {
-    const double g = mm(x, x);               // its diagonal: the columns' sums of squares
-    return mm(1.0, mm(t.i == t.j ? g : 0.0, 1.0));
+// x on all lanes of the lane's chain
+__device__ __forceinline__ bool all_of(bool x, const Lane& t) {
+    return (__ballot(!x) & (0x000f000f000f000full << (4 * t.b))) == 0;
+}
+// what a covariance P adds to C by way of A, A P A^T, is at most 2^-60 of C in
+// every variance (A by its transpose)
+__device__ __forceinline__ bool negligible(double AT, double P, double C, const Lane& t) {
+    return all_of(t.i != t.j || mm(AT, mm(P, AT)) <= kTiny * C, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -214,9 +218,7 @@ __device__ __forceinline__ bool agree(double P, double m, double P2, double m2, 
     const double zz = t.j == 0 && di > 0.0 ? m2 / sqrt(di) : 0.0;
     const double z = col<0>(row<0>(mm(zz, zz), t));
     const double dP = P - P2, dm = t.j == 0 ? m - m2 : 0.0;
-    const bool same = dP * dP <= kSame * kSame * di * dj && dm * dm <= kSame * kSame * di * (1.0 + z);
-    const unsigned long long off = __ballot(!same);
-    return (off & (0x000f000f000f000full << (4 * t.b))) == 0;
+    return all_of(dP * dP <= kSame * kSame * di * dj && dm * dm <= kSame * kSame * di * (1.0 + z), t);
 }
 
 // ---------------------------------------------------------------------------
@@ -313,10 +315,10 @@ __global__ __launch_bounds__(1024) void k_chain_setup(Args a) {
 
 // ---------------------------------------------------------------------------
 // Settled covariances of time-invariant models, four a wave: the filtering
-// element of one step is doubled (Lemma 2 on equal elements) until
-// |A|^2 (|P0| + |C|) <= 2^-60 |C|, after which every filtered covariance is C to
-// the last bit of FP64, and the smoothing element (Lemma 4) the same way; the
-// powers then give the number of steps to 16.
+// element of one step is doubled (Lemma 2 on equal elements) until each variance
+// of A (P0 + C) A^T is at most 2^-60 of C's, after which every filtered covariance
+// is C to FP64's rounding (see steady.hpp), and the smoothing element (Lemma 4)
+// the same way; the powers then give the number of steps to 16.
 // Bound by the latency of up to 2 kMaxLog dependent combines.
 // ---------------------------------------------------------------------------
 template <int NX, int NY>
@@ -340,7 +342,6 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
         C = sym(mm(-Kt, HQ, Q), t);
         J = sym(mm(G, mm(Si, G)), t);
     }
-    const double p0 = sqrt(sumsq(P0, t));
     int lf = -1, le = -1;
     __shared__ double lev[kMaxLog][3][64];            // A, C, J of 2^l steps
     const int lane = threadIdx.x;
@@ -353,10 +354,7 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
         An = mm(trans(AX, t), Ai);
         Cn = sym(mm(trans(mm(trans(AX, t), Ci), t), trans(Aj, t), Cj), t);
     };
-    auto settled = [&](double An, double Cn) {
-        const double fa = sumsq(An, t), fc = sqrt(sumsq(Cn, t));
-        return fa * (p0 + fc) <= kTiny * fc;
-    };
+    auto settled = [&](double An, double Cn) { return negligible(trans(An, t), P0 + Cn, Cn, t); };
     for (int l = 1; l <= kMaxLog; ++l) {
         lev[l - 1][0][lane] = A;
         lev[l - 1][1][lane] = C;
@@ -398,16 +396,14 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
         const double EFP = mm(ET, mm(FT, P));
         L = sym(P - EFP, t);
     }
-    const double fp = sqrt(sumsq(P, t));
     for (int l = 1; l <= kMaxLog; ++l) {
         lev[l - 1][0][lane] = E2;
         lev[l - 1][1][lane] = L;
         const double Ln = sym(mm(E2, mm(L, E2), L), t), En = mm(trans(E2, t), E2);     // (E E)^T
-        const double fe = sumsq(En, t), fl = sqrt(sumsq(Ln, t));
-        const bool on = le < 0;
+        const bool on = le < 0, good = negligible(En, P, Ln, t);
         L = on ? Ln : L;
         E2 = on ? En : E2;
-        if (on && l >= 2 && fe * fp <= kTiny * fl) le = l;
+        if (on && l >= 2 && good) le = l;
         if (!__any(le < 0)) break;
     }
     int e16 = 16;
@@ -416,8 +412,7 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
         for (int l = kMaxLog - 1; l >= 4; --l) {
             const double El = lev[l][0][lane], Ll = lev[l][1][lane];
             const double Ln = sym(mm(Ec, mm(Ll, Ec), Lc), t), En = mm(trans(El, t), Ec);   // E_c L_l E_c^T + L_c, (E_c E_l)^T
-            const double fe = sumsq(En, t), fl = sqrt(sumsq(Ln, t));
-            const bool start = l == le - 1, on = l < le - 1 && !(fe * fp <= kTiny * fl);
+            const bool fine = negligible(En, P, Ln, t), start = l == le - 1, on = l < le - 1 && !fine;
             Ec = start ? El : (on ? En : Ec);
             Lc = start ? Ll : (on ? Ln : Lc);
             e16 += start || on ? 1 << l : 0;
@@ -433,9 +428,8 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
     o[64] = ET;
     o[80] = L;
     ok = ok && lf > 0 && le > 0;
-    const unsigned long long off = __ballot(!ok);
+    const bool good = all_of(ok, t) && n16 <= kLongest && e16 <= kLongest;
     if (t.i == 0 && t.j == 0) {
-        const bool good = (off & (0x000f000f000f000full << (4 * t.b))) == 0 && n16 <= kLongest && e16 <= kLongest;
         if (!good) a.ctl[0] = 0;
         a.head[2 * b] = good ? n16 : 0;
         a.head[2 * b + 1] = good ? e16 : 0;

@@ -89,6 +89,17 @@ template <int KX>
 __device__ __forceinline__ f64x4 ele(const f64x4& ET, const f64x4& L, const f64x4& add, double* st) {
     return symt(mm<KX>(mm<KX>(L, ET), ET), add, st);
 }
+// whether what a covariance P adds to C by way of A, A P A^T, is at most f of C in
+// every variance (AT: the tile of A^T)
+template <int KX>
+__device__ __forceinline__ bool negligible(const f64x4& AT, const f64x4& P, const f64x4& C, double f, int n) {
+    return diagonal_below(mm<KX>(AT, mm<KX>(P, AT)), C, f, n);
+}
+template <int KX>
+__device__ __forceinline__ bool meets(const f64x4& x, const f64x4& y) {
+    const f64x4 d = diagonal(y);
+    return steady::meets(x, y, mm<KX>(d, ones()), mm<KX>(ones(), d));
+}
 __device__ __forceinline__ void store_gain(double* X, const f64x4& K, int n, int m) {
     const int li = lane_i(), lk = lane_k();
 #pragma unroll
@@ -129,23 +140,23 @@ __global__ __launch_bounds__(64) void k_st_double(Args a) {
     store_tile(a.powF, A, n);
     store_tile(a.powF + n2, C, n);
     store_tile(a.powF + 2 * n2, J, n);
-    const double p0 = sqrt(sumsq(P0));
     int lf = 0, le = 0;
     bool settled = false;
+    f64x4 AT = tr(A, st);
 #pragma unroll 1
     for (int l = 1; (1 << l) <= a.N && ok; ++l) {
         const f64x4 NT = inv_ijc<KX>(C, J, I, st, n, ok);
-        const f64x4 X1 = mm<KX>(NT, A), X3 = mm<KX>(NT, C), JA = mm<KX>(J, A), AT = tr(A, st);
+        const f64x4 X1 = mm<KX>(NT, A), X3 = mm<KX>(NT, C), JA = mm<KX>(J, A);
         A = mm<KX>(AT, X1);
         C = symt(mm<KX>(AT, mm<KX>(X3, AT)), C, st);
+        AT = tr(A, st);
         J = symt(mm<KX>(X1, JA), J, st);
         double* rec = a.powF + (int64_t)l * 3 * n2;
         store_tile(rec, A, n);
         store_tile(rec + n2, C, n);
         store_tile(rec + 2 * n2, J, n);
-        const double fa = sumsq(A), fc = sqrt(sumsq(C));
         lf = l;
-        if ((1 << l) >= kRun && fa * (p0 + fc) <= kTiny * fc) {
+        if ((1 << l) >= kRun && negligible<KX>(AT, P0 + C, C, kTiny, n)) {
             settled = true;
             break;
         }
@@ -164,7 +175,6 @@ __global__ __launch_bounds__(64) void k_st_double(Args a) {
     store_tile(a.star + star_E(n, x.m), tr(ET, st), n);
     store_tile(a.star + star_L(n, x.m), L, n);
     // smoothing elements of 2^l settled steps
-    const double fp = sqrt(sumsq(P));
     settled = false;
 #pragma unroll 1
     for (int l = 0; (1 << l) <= a.N && ok; ++l) {
@@ -177,8 +187,7 @@ __global__ __launch_bounds__(64) void k_st_double(Args a) {
         store_tile(a.powE + (int64_t)l * 2 * n2, E, n);
         store_tile(a.powE + (int64_t)l * 2 * n2 + n2, L, n);
         le = l;
-        const double fe = sumsq(ET), fl = sqrt(sumsq(L));
-        if ((1 << l) >= kRun && fe * fp <= kTiny * fl) {
+        if ((1 << l) >= kRun && negligible<KX>(ET, P, L, kTiny, n)) {
             settled = true;
             break;
         }
@@ -266,13 +275,15 @@ __global__ __launch_bounds__(64) void k_st_tables(Args a) {
             store_tile(a.tTail + (int64_t)j * n2, Ps, n);
             Ps = ele<KX>(ET, Ps, L, st);
         }
+        if (j0 + kRun == 1 << a.ctl[2] && !meets<KX>(Ps, load_tile(a.star + star_Ps(n, m), n, n, n)) && threadIdx.x == 0)
+            atomicExch(&a.ctl[0], 0);
         return;
     }
     const int k0 = blk * kRun;
     const Model16 x = load_model(a);
     f64x4 P = load_tile(a.P0, n, n, n);
     const f64x4 Pstar = load_tile(a.star + star_P(n, m), n, n, n);
-    const double most = kSpare * (sqrt(sumsq(P)) + sqrt(sumsq(Pstar)));
+    const f64x4 AnT = load_tile_t(a.powF + (int64_t)a.ctl[1] * 3 * n2, n, n, n);       // of the steps that it takes to settle
     if (k0 >> a.ctl[1]) {
         P = Pstar;
     } else {
@@ -303,7 +314,7 @@ __global__ __launch_bounds__(64) void k_st_tables(Args a) {
             }
         }
         update<KX, KY>(x, Pm, st, ok, P, Kt, Phi, c);
-        ok = ok && sqrt(sumsq(P)) <= most;
+        ok = ok && negligible<KX>(AnT, P, Pstar, kSpare * kTiny, n);
         Pa = mm<KX>(tr(Phi, st), Pa);
         store_tile(a.tP + (int64_t)k * n2, P, n);
         store_tile(a.tPhi + (int64_t)k * n2, Phi, n);
@@ -319,6 +330,7 @@ __global__ __launch_bounds__(64) void k_st_tables(Args a) {
             store_tile(a.tL + (int64_t)(nh - 1) * n2, load_tile(a.star + star_L(n, m), n, n, n), n);
         }
     }
+    if (k0 + kRun == 1 << a.ctl[1]) ok = ok && meets<KX>(P, Pstar);
     if (!ok && threadIdx.x == 0) atomicExch(&a.ctl[0], 0);
 }
 

@@ -4,8 +4,12 @@
 // The covariances of a time-invariant model do not depend on the
 // measurements, and for a model the filter can follow they settle: the block
 // element of n steps (Lemma 2 applied to equal elements) has P_k = A X A^T + C
-// with X <= P_{k-n}, so once |A|^2 |P| is below the rounding of C every later
-// filtered covariance equals C in every bit that FP64 holds.  The same holds
+// with X <= P_{k-n}, so once the remainder A X A^T is below the rounding of C
+// every later filtered covariance is C to FP64's rounding.  Below it means entry
+// by entry: the remainder is positive semidefinite, so that its entry (i, j) is at
+// most the root of the product of two of its diagonal, and each of those is held
+// against the variance of its own state (states of different units, or one that
+// is hardly driven, have variances many orders apart).  The same holds
 // for the smoothing element (Lemma 4): Ps_k = E^n Ps_{k+n} E^nT + L.  The
 // setup finds the smallest such power of two n by recursive doubling (a chain
 // of log2 n combines instead of one O(nx^3) combine per step), forms

@@ -28,9 +28,9 @@ constexpr int kLargePowers = 9;       // L .. 256 L
 // ---------------------------------------------------------------------------
 template <int NT>
 struct Eng {
-    static constexpr int kTiles = NT * NT, kWaves = NT * NT;
-    static constexpr int kLds = (2 * kTiles + 1) * kTile + kWaves + 8;      // doubles
-    double *b0, *b1, *db, *red;
+    static constexpr int kTiles = NT * NT;
+    static constexpr int kLds = (2 * kTiles + 1) * kTile + 8;      // doubles
+    double *b0, *b1, *db;
     int* flag;
     int r, c, w, n, m;
 
@@ -38,8 +38,7 @@ struct Eng {
         b0 = lds;
         b1 = b0 + kTiles * kTile;
         db = b1 + kTiles * kTile;
-        red = db + kTile;
-        flag = reinterpret_cast<int*>(red + kWaves);
+        flag = reinterpret_cast<int*>(db + kTile);
         w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         r = w / NT;
         c = w % NT;
@@ -96,16 +95,6 @@ struct Eng {
         return t;
     }
     __device__ __forceinline__ f64x4 symt(const f64x4& x, const f64x4& add) const { return sym(x, tr(x), add); }
-    __device__ __forceinline__ double sum2(const f64x4& x) const {
-        const double s = sumsq(x);
-        if ((threadIdx.x & 63) == 0) red[w] = s;
-        __syncthreads();
-        double t = 0.0;
-#pragma unroll
-        for (int i = 0; i < kWaves; ++i) t += red[i];
-        __syncthreads();
-        return t;
-    }
     __device__ __forceinline__ bool any(bool x) const {
         if (threadIdx.x == 0) *flag = 0;
         __syncthreads();
@@ -146,6 +135,15 @@ struct Eng {
     // E L E^T + add, E by its transpose
     __device__ __forceinline__ f64x4 ele(const f64x4& ET, const f64x4& L, const f64x4& add) const {
         return symt(xty(xty(L, ET), ET), add);
+    }
+    // (negligible, meets: as in steady.hip)
+    __device__ __forceinline__ bool negligible(const f64x4& AT, const f64x4& P, const f64x4& C, double f) const {
+        const f64x4 R = xty(AT, xty(P, AT));
+        return !any(r == c && !diagonal_below(R, C, f, n - 16 * r));
+    }
+    __device__ __forceinline__ bool meets(const f64x4& x, const f64x4& y) const {
+        const f64x4 d = r == c ? diagonal(y) : zero4(), di = xty(d, ones()), dj = xty(ones(), d);
+        return !any(!steady::meets(x, y, di, dj));
     }
     // (M^T)^-1 for M = I + C J: kept when its residual is below 1e-11 in every entry
     __device__ __forceinline__ f64x4 inv_ijc(const f64x4& C, const f64x4& J, bool& ok) const {
@@ -298,23 +296,24 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_double(Args a) {
     e.st(a.powF, A, n, n);
     e.st(a.powF + n2, C, n, n);
     e.st(a.powF + 2 * n2, J, n, n);
-    const double p0 = sqrt(e.sum2(e.ld(a.P0, n, n)));
+    const f64x4 P0 = e.ld(a.P0, n, n);
     int lf = 0, le = 0;
     bool settled = false;
+    f64x4 AT = e.tr(A);
 #pragma unroll 1
     for (int l = 1; (1 << l) <= a.N && ok; ++l) {
         const f64x4 N = e.inv_ijc(C, J, ok);
-        const f64x4 X1 = e.xty(N, A), X3 = e.xty(N, C), JA = e.xty(J, A), AT = e.tr(A);
+        const f64x4 X1 = e.xty(N, A), X3 = e.xty(N, C), JA = e.xty(J, A);
         A = e.xty(AT, X1);
         C = e.symt(e.xty(AT, e.xty(X3, AT)), C);
         J = e.symt(e.xty(X1, JA), J);
+        AT = e.tr(A);
         double* rec = a.powF + (int64_t)l * 3 * n2;
         e.st(rec, A, n, n);
         e.st(rec + n2, C, n, n);
         e.st(rec + 2 * n2, J, n, n);
-        const double fa = e.sum2(A), fc = sqrt(e.sum2(C));
         lf = l;
-        if ((1 << l) >= kRun && fa * (p0 + fc) <= kTiny * fc) {
+        if ((1 << l) >= kRun && e.negligible(AT, P0 + C, C, kTiny)) {
             settled = true;
             break;
         }
@@ -331,7 +330,6 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_double(Args a) {
     gain_offset(e, a, Kt, a.star + star_c(n, m));
     e.st(a.star + star_E(n, m), e.tr(ET), n, n);
     e.st(a.star + star_L(n, m), L, n, n);
-    const double fp = sqrt(e.sum2(P));
     settled = false;
 #pragma unroll 1
     for (int l = 0; (1 << l) <= a.N && ok; ++l) {
@@ -344,8 +342,7 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_double(Args a) {
         e.st(a.powE + (int64_t)l * 2 * n2, E, n, n);
         e.st(a.powE + (int64_t)l * 2 * n2 + n2, L, n, n);
         le = l;
-        const double fe = e.sum2(ET), fl = sqrt(e.sum2(L));
-        if ((1 << l) >= kRun && fe * fp <= kTiny * fl) {
+        if ((1 << l) >= kRun && e.negligible(ET, P, L, kTiny)) {
             settled = true;
             break;
         }
@@ -389,6 +386,7 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_tables(Args a) {
     if (nh == 0) return;
     const Eng<NT> e(lds, a);
     const int nrun = nh / kRun, n = a.nx, n2 = n * n, m = a.ny;
+    const int lf = a.ctl[1], le = a.ctl[2];
     int blk = blockIdx.x;
     if (blk < 2) {
         if (blk == 1 && !a.smooth) return;
@@ -408,7 +406,7 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_tables(Args a) {
     if (blk >= nrun) {                       // tail
         const int j0 = (blk - nrun) * kRun;
         f64x4 Ps;
-        if (j0 >> a.ctl[2]) {
+        if (j0 >> le) {
             Ps = e.ld(a.star + star_Ps(n, m), n, n);
         } else {
             Ps = e.ld(a.star + star_P(n, m), n, n);
@@ -425,14 +423,16 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_tables(Args a) {
             e.st(a.tTail + (int64_t)j * n2, Ps, n, n);
             Ps = e.ele(ET, Ps, L);
         }
+        if (j0 + kRun == 1 << le && !e.meets(Ps, e.ld(a.star + star_Ps(n, m), n, n)) && threadIdx.x == 0)
+            atomicExch(&a.ctl[0], 0);
         return;
     }
     const int k0 = blk * kRun;
     const ModelL<NT> x = load_model(e, a);
     f64x4 P = e.ld(a.P0, n, n);
     const f64x4 Pstar = e.ld(a.star + star_P(n, m), n, n);
-    const double most = kSpare * (sqrt(e.sum2(P)) + sqrt(e.sum2(Pstar)));
-    if (k0 >> a.ctl[1]) {
+    const f64x4 AnT = e.ldt(a.powF + (int64_t)lf * 3 * n2, n, n);       // of the steps that it takes to settle
+    if (k0 >> lf) {
         P = Pstar;
     } else {
 #pragma unroll 1
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_tables(Args a) {
             EaT = e.xty(E, EaT);             // (E_a E)^T
         }
         update(e, x, Pm, ok, P, Kt, Phi);
-        ok = ok && sqrt(e.sum2(P)) <= most;
+        ok = e.negligible(AnT, P, Pstar, kSpare * kTiny) && ok;
         Pa = e.xty(e.tr(Phi), Pa);
         e.st(a.tP + (int64_t)k * n2, P, n, n);
         e.st(a.tPhi + (int64_t)k * n2, Phi, n, n);
@@ -475,6 +475,7 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_tables(Args a) {
             e.st(a.tL + (int64_t)(nh - 1) * n2, e.ld(a.star + star_L(n, m), n, n), n, n);
         }
     }
+    if (k0 + kRun == 1 << lf) ok = e.meets(P, Pstar) && ok;
     if (!ok && threadIdx.x == 0) atomicExch(&a.ctl[0], 0);
 }
 

@@ -14,11 +14,14 @@ namespace steady {
 
 using namespace w16;
 
-// how small |A|^2 |P| has to be against |C|: FP64 rounding with 2^7 to spare
-// for covariances of the head above the prior and the settled one (checked
-// when the head is formed)
+// how small each variance of A (P0 + C) A^T has to be against C's: FP64 rounding
+// with 2^7 to spare for covariances of the head above the prior and the settled
+// one (checked when the head is formed)
 constexpr double kTiny = 8.673617379884035e-19;      // 2^-60
 constexpr double kSpare = 128.0;
+// and how far the last covariance of the head (the tail), which is formed step by
+// step, may be from the settled one, which is doubled: two digits inside the parity bar
+constexpr double kMeet = 1e-11;
 
 // ---------------------------------------------------------------------------
 // tiles with KX (KY) K-slices: rows and columns beyond 4 KX are zero
@@ -38,16 +41,31 @@ __device__ __forceinline__ f64x4 shift(const f64x4& x) {
     for (int v = 0; v < KX; ++v) t[v] = UP ? dpp0<0x110 + D>(x[v]) : dpp0<0x100 + D>(x[v]);
     return t;
 }
-__device__ __forceinline__ double wave_sum(double x) {
-    x += dpp0<0x111>(x);
-    x += dpp0<0x112>(x);
-    x += dpp0<0x114>(x);
-    x += dpp0<0x118>(x);         // the last lane of every row of 16 holds the row's sum
-    return (readlane_d(x, 15) + readlane_d(x, 31)) + (readlane_d(x, 47) + readlane_d(x, 63));
+
+// tiles: each diagonal entry of x is at most f times y's (the first n)
+__device__ __forceinline__ bool diagonal_below(const f64x4& x, const f64x4& y, double f, int n) {
+    const int li = lane_i(), lk = lane_k();
+    bool off = false;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) off |= 4 * v + lk == li && li < n && !(x[v] <= f * y[v]);
+    return !__any(off);
 }
-__device__ __forceinline__ double sumsq(const f64x4& t) {
-    return wave_sum(fma(t[0], t[0], t[1] * t[1]) + fma(t[2], t[2], t[3] * t[3]));
+// x equals y, each entry to kMeet of the root of the product of its variances (di,
+// dj: those of y along the rows and the columns)
+__device__ __forceinline__ bool meets(const f64x4& x, const f64x4& y, const f64x4& di, const f64x4& dj) {
+    bool off = false;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) off |= !((x[v] - y[v]) * (x[v] - y[v]) <= kMeet * kMeet * (di[v] * dj[v]));
+    return !__any(off);
 }
+__device__ __forceinline__ f64x4 diagonal(const f64x4& x) {
+    const int li = lane_i(), lk = lane_k();
+    f64x4 t;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) t[v] = 4 * v + lk == li ? x[v] : 0.0;
+    return t;
+}
+__device__ __forceinline__ f64x4 ones() { return f64x4{1.0, 1.0, 1.0, 1.0}; }
 
 // Inverse by Gauss-Jordan elimination without pivoting, as w16::inv_diag, with
 // a constant number NP of pivots (rows beyond the matrix hold the identity), so

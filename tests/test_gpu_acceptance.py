@@ -84,3 +84,48 @@ def test_subnormal_last_step(pks):
     # the weights exp(-712), exp(-713) are subnormal: 48 and 47 bits
     ref = oracle.hmm_fb(Pi, p0, L)
     assert np.max(np.abs(out[0] - ref["alpha"])) <= 1e-9 and np.max(np.abs(out[2] - ref["gamma"])) <= 1e-9
+
+
+# ---------------------------------------------------------------------------
+# settled covariances: every entry, not the norm
+# ---------------------------------------------------------------------------
+def weakly_driven(nx, ny, slow, q):
+    """The last state decays slowly, is hardly driven and not seen: its variance
+    falls from 1 to about 6 q, far below the others'."""
+    f = np.r_[np.linspace(0.9, 0.8, nx - 1), slow]
+    H = np.eye(ny, nx)
+    return wl.Model(np.diag(f), np.diag(np.r_[np.ones(nx - 1), q]), H, np.eye(ny), np.zeros(nx), np.eye(nx))
+
+
+def entry_errors(model, y, P, Ps):
+    ref = oracle.kf_rts(model.F, model.Q, model.H, model.R, model.m0, model.P0, y)
+    return [np.max(np.abs(a[:, -1, -1] / ref[k][:, -1, -1] - 1.0)) for a, k in ((P, "P"), (Ps, "Ps"))]
+
+
+@pytest.mark.parametrize("nx,ny,T", [(3, 2, 500000), (4, 2, 250000), (8, 3, 9000), (16, 8, 9000), (20, 5, 8200), (40, 9, 8200)])
+@pytest.mark.parametrize("q", [1e-12, 1e-14])
+def test_settled_entry_by_entry(pks, nx, ny, T, q):
+    model = weakly_driven(nx, ny, 0.9195, q)
+    y = np.random.default_rng(nx).standard_normal((T, ny))
+    ws = pks.workspace(nx, ny, T, 1, "fp64")
+    _, P, _, Ps = pks.filter_smooth(pks.to_device(model), torch.as_tensor(y).cuda(), "fp64", ws=ws)
+    torch.cuda.synchronize()
+    assert int(ws[:256].cpu().numpy().view(np.int32)[CTL]) > 0          # settles, after 512 steps
+    errors = entry_errors(model, y, P.cpu().numpy(), Ps.cpu().numpy())
+    assert max(errors) <= TOL["fp64"], errors
+
+
+@pytest.mark.parametrize("nx", [3, 4])
+@pytest.mark.parametrize("q", [1e-12, 1e-14])
+def test_settled_entry_by_entry_each_its_model(pks, nx, q):
+    lengths, model = [400000, 700000], weakly_driven(nx, 2, 0.9, q)
+    packed = wl.Model(*(np.stack([getattr(model, f)] * 2) for f in ("F", "Q", "H", "R", "m0", "P0")))
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    y = np.random.default_rng(nx).standard_normal((int(offsets[-1]), 2))
+    plan = pks.Plan(pks.to_device(packed, per_sequence=True), torch.as_tensor(y).cuda(), torch.as_tensor(offsets).cuda(), "fp64")
+    _, P, _, Ps = plan.launch()
+    torch.cuda.synchronize()
+    assert int(plan.ws[:256].cpu().numpy().view(np.int32)[CTL]) > 0     # settles, after 352 steps at most
+    for s, e in zip(offsets[:-1], offsets[1:]):
+        errors = entry_errors(model, y[s:e], P[s:e].cpu().numpy(), Ps[s:e].cpu().numpy())
+        assert max(errors) <= TOL["fp64"], errors
