@@ -19,6 +19,7 @@ namespace {
 constexpr int kAhead = 4;            // steps of a group; their loads are issued a group or two before
 constexpr double kSame = 5.684341886080802e-14;       // 2^-44
 constexpr double kTiny = 8.673617379884035e-19;       // 2^-60
+constexpr double kMeet = 1e-11;      // how far a head's last covariance, formed step by step, may be from the doubled one
 constexpr int kMaxLog = 9;           // settled after at most 2^kMaxLog steps
 constexpr int kLongest = 384;        // and no later than this (a step of a head is 0.33 us of the filter, 0.5 of the smoother)
 
@@ -211,6 +212,11 @@ __device__ __forceinline__ Chain chain_of(const Args& a, int64_t c) {
     return x;
 }
 
+// P equals P2, each entry to kMeet of the root of the product of its variances
+__device__ __forceinline__ bool meets(double P, double P2, const Lane& t) {
+    const double D = t.i == t.j ? P2 : 0.0, di = mm(D, 1.0), dj = mm(1.0, D);
+    return all_of((P - P2) * (P - P2) <= kMeet * kMeet * di * dj, t);
+}
 // moments (P, m) and (P2, m2) agree: differences against the standard deviations,
 // the mean's against the size of the whole mean as well (its rounding is)
 __device__ __forceinline__ bool agree(double P, double m, double P2, double m2, const Lane& t) {
@@ -348,8 +354,12 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
     auto combine = [&](double Ai, double Ci, double Aj, double Cj, double Jj, double& An, double& Cn, double& X, bool& fine) {
         const double M = mm(Ci, Jj, I);                       // I + C_i J_j
         X = inv_general<NX>(M, t, fine);
-        // one Newton step: the elimination has no row exchanges
-        X = mm(trans(X, t), I - mm(trans(M, t), X), X);
+        // one Newton step, as the elimination has no row exchanges: leading minors of
+        // I + C J may be small where it is not (correlated noise), and the step needs
+        // a residual that is
+        const double res = I - mm(trans(M, t), X);
+        fine &= fabs(res) <= 1e-8;
+        X = mm(trans(X, t), res, X);
         const double AX = mm(trans(Aj, t), X);                // A_j (I + C_i J_j)^-1
         An = mm(trans(AX, t), Ai);
         Cn = sym(mm(trans(mm(trans(AX, t), Ci), t), trans(Aj, t), Cj), t);
@@ -379,7 +389,7 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
             bool fine = true;
             double An, Cn, X;
             combine(Ac, Cc, lev[l][0][lane], lev[l][1][lane], lev[l][2][lane], An, Cn, X, fine);
-            const bool start = l == lf - 1, on = l < lf - 1 && !settled(An, Cn);
+            const bool done = settled(An, Cn) && all_of(fine, t), start = l == lf - 1, on = l < lf - 1 && !done;
             Ac = start ? lev[l][0][lane] : (on ? An : Ac);
             Cc = start ? lev[l][1][lane] : (on ? Cn : Cc);
             n16 += start || on ? 1 << l : 0;
@@ -889,6 +899,10 @@ __global__ __launch_bounds__(64) void k_chain_filter_ti(Args a, int pass, int wr
                 oP.move(4);
             }
             finish(o);
+            if (__any(k == settled && k <= e)) {
+                const bool same = meets(P, Pstar, t);
+                ok &= same | !(k == settled && k <= e);
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q) cur[q] = nxt[q];
         }
@@ -1049,6 +1063,11 @@ __global__ __launch_bounds__(64) void k_chain_smoother_ti(Args a, int pass, int 
                         double mn = ms, Psn = Ps;
                         smoother_step(ET[q], Pp[q], mp[q], mq[q], P[q], mn, Psn);
                         ms = on ? mn : ms;
+                        const bool enters = on && kq == last && kq >= first && k >= s;
+                        if (__any(enters)) {
+                            const bool same = meets(Psn, Psstar, t);
+                            ok &= same | !enters;
+                        }
                         Ps = on ? (kq >= first && kq <= last ? Psstar : Psn) : Ps;
                         o[q] = t.j == j ? ms : o[q];
                         oP.put(4 * j + q, sym(Ps, t), kq < end && mine);

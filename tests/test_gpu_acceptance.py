@@ -129,3 +129,48 @@ def test_settled_entry_by_entry_each_its_model(pks, nx, q):
     for s, e in zip(offsets[:-1], offsets[1:]):
         errors = entry_errors(model, y[s:e], P[s:e].cpu().numpy(), Ps[s:e].cpu().numpy())
         assert max(errors) <= TOL["fp64"], errors
+
+
+def small_pivot_model(seed, pivot):
+    """Noise so correlated that the first entry of I + C J, one step's element with
+    itself, is `pivot`."""
+    rng = np.random.default_rng(seed)
+    F = rng.standard_normal((4, 4))
+    F *= 0.8 / np.max(np.abs(np.linalg.eigvals(F)))
+    G = rng.standard_normal((4, 4))
+    Q, H, R = G @ G.T + 1e-3 * np.eye(4), rng.standard_normal((2, 4)), 0.1 * np.eye(2)
+
+    def at(t):
+        D = np.diag([t, 1.0, 1.0, 1.0])
+        S = H @ (D @ Q @ D) @ H.T + R
+        K = D @ Q @ D @ H.T @ np.linalg.inv(S)
+        return 1.0 + ((D @ Q @ D - K @ S @ K.T) @ (F.T @ H.T @ np.linalg.inv(S) @ H @ F))[0, 0]
+
+    ts = np.linspace(0.05, 3.0, 60)
+    v = [at(t) for t in ts]
+    i = int(np.nonzero(np.sign(v[:-1]) != np.sign(v[1:]))[0][0])
+    lo, hi, sign = ts[i], ts[i + 1], np.sign(v[i])
+    for _ in range(200):
+        mid = 0.5 * (lo + hi)
+        lo, hi = (mid, hi) if np.sign(at(mid) - sign * pivot) == sign else (lo, mid)
+    D = np.diag([lo, 1.0, 1.0, 1.0])
+    return wl.Model(F, D @ Q @ D, H, R, np.zeros(4), np.eye(4))
+
+
+@pytest.mark.parametrize("seed", [65, 222])
+@pytest.mark.parametrize("pivot", [1e-9, 1e-13])
+def test_small_pivots(pks, seed, pivot):
+    """Elimination without row exchanges loses |log10 pivot| digits of the settled
+    covariance: 7e-6 of it at 1e-13."""
+    lengths, model = [400000, 700000], small_pivot_model(seed, pivot)
+    packed = wl.Model(*(np.stack([getattr(model, f)] * 2) for f in ("F", "Q", "H", "R", "m0", "P0")))
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    y = np.random.default_rng(seed).standard_normal((int(offsets[-1]), 2))
+    plan = pks.Plan(pks.to_device(packed, per_sequence=True), torch.as_tensor(y).cuda(), torch.as_tensor(offsets).cuda(), "fp64")
+    out = plan.launch()
+    torch.cuda.synchronize()
+    s, e = offsets[:2]
+    ref = oracle.kf_rts(model.F, model.Q, model.H, model.R, model.m0, model.P0, y[s:e])
+    for k, v in zip(("m", "P", "ms", "Ps"), out):
+        err = wl.max_rel_err(v[s:e].cpu().numpy(), ref[k])
+        assert err <= TOL["fp64"], (k, err)
