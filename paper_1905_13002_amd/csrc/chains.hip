@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "chains.hpp"
 #include "tile16.hpp"
@@ -17,7 +18,15 @@ namespace chains {
 namespace {
 
 constexpr int kAhead = 4;            // steps of a group; their loads are issued a group or two before
-constexpr double kSame = 5.684341886080802e-14;       // 2^-44
+// Distances in the units of agree(), squared.  Two recursions of a CV model that
+// have met stay within 2^-51 of each other (17000 samples): four times that is
+// taken as having met.  Of an ill-conditioned model (a measurement much better than
+// the prediction, or a badly conditioned S) they stay as far as 2^-45 apart, and no
+// warm-up brings them closer: chains that differ by more than kSame are run again
+// from their predecessor's end, a whole chain's length of steps further on, and
+// then kRounding is enough where the first difference, `near`, says that what was
+// not forgotten by then is by now (below 2^-50).
+constexpr double kSame = 0x1p-98, kRounding = 0x1p-88;
 constexpr double kTiny = 8.673617379884035e-19;       // 2^-60
 constexpr double kMeet = 1e-11;      // how far a head's last covariance, formed step by step, may be from the doubled one
 constexpr int kMaxLog = 9;           // settled after at most 2^kMaxLog steps
@@ -219,12 +228,12 @@ __device__ __forceinline__ bool meets(double P, double P2, const Lane& t) {
 }
 // moments (P, m) and (P2, m2) agree: differences against the standard deviations,
 // the mean's against the size of the whole mean as well (its rounding is)
-__device__ __forceinline__ bool agree(double P, double m, double P2, double m2, const Lane& t) {
+__device__ __forceinline__ bool agree(double P, double m, double P2, double m2, double far, const Lane& t) {
     const double D = t.i == t.j ? P2 : 0.0, di = mm(D, 1.0), dj = mm(1.0, D);
     const double zz = t.j == 0 && di > 0.0 ? m2 / sqrt(di) : 0.0;
     const double z = col<0>(row<0>(mm(zz, zz), t));
     const double dP = P - P2, dm = t.j == 0 ? m - m2 : 0.0;
-    return all_of(dP * dP <= kSame * kSame * di * dj && dm * dm <= kSame * kSame * di * (1.0 + z), t);
+    return all_of(dP * dP <= far * di * dj && dm * dm <= far * di * (1.0 + z), t);
 }
 
 // ---------------------------------------------------------------------------
@@ -235,8 +244,11 @@ struct Row {
 };
 template <int NY>
 __device__ __forceinline__ void filter_step(const Row& x, const Lane& t, double& m, double& P, bool& ok) {
+    // F P F^T + Q, symmetric in every bit: the two products are each other's
+    // transposes.  (An antisymmetric part, once there, does not decay: without this two
+    // recursions stay 2^-46 apart for good, with it they meet in every bit.)
     const double W = mm(P, x.FT), mp = mm(x.FT, m, x.u);
-    const double Pp = mm(x.FT, W, x.Q);                       // F P F^T + Q
+    const double Pp = 0.5 * (mm(x.FT, W, x.Q) + mm(W, x.FT, x.Q));
     const double V = mm(Pp, x.HT), VT = mm(x.HT, Pp);         // Pp H^T, H Pp
     const double Si = inv<NY>(mm(x.HT, V, x.R), t, ok);
     const double r = mm(x.HT, -mp, x.y);
@@ -270,6 +282,24 @@ __device__ __forceinline__ void load_state(const double* p, int64_t c, const Lan
 __device__ __forceinline__ void store_state(double* p, int64_t c, const Lane& t, double P, double m) {
     p[c * kState + 4 * t.i + t.j] = P;
     p[c * kState + 16 + 4 * t.i + t.j] = m;
+}
+
+// The second pass: whether a chain that entered with (P, m) runs again from its
+// neighbour's end (P2, m2); one that does not keeps its own end
+__device__ __forceinline__ bool again(const Args& a, const Chain& x, double P, double m, double P2, double m2, double near,
+                                      bool edge, const Lane& t) {
+    const bool same = agree(P, m, P2, m2, kSame, t), close = agree(P, m, P2, m2, near, t);
+    if (x.live && t.i == 0 && t.j == 0) a.forgets[x.c] = close;
+    if (x.live && (same || edge)) {
+        load_state(a.end[0], x.c, t, P, m);
+        store_state(a.end[1], x.c, t, P, m);
+    }
+    return x.live && !same && !edge;
+}
+// The means of a settled model lose 30 bits in the steps that the covariances take
+// to settle: what l steps bring below 2^-50
+__device__ __forceinline__ double near_of(int64_t l, int head) {
+    return exp2(2.0 * (fmin(30.0 * (double)l / head, 30.0) - 50.0));
 }
 
 // ---------------------------------------------------------------------------
@@ -472,12 +502,7 @@ __global__ __launch_bounds__(64) void k_chain_filter_tv(Args a, int pass) {
         double oP, om;
         load_state(a.end[0], x.s > x.lo ? x.c - 1 : x.c, t, P, m);
         load_state(a.entry, x.c, t, oP, om);
-        const bool same = agree(oP, om, P, m, t) || x.s == x.lo;
-        if (same && x.live) {
-            load_state(a.end[0], x.c, t, oP, om);
-            store_state(a.end[1], x.c, t, oP, om);
-        }
-        todo = todo && !same;
+        todo = again(a, x, oP, om, P, m, a.near, x.s == x.lo, t);
         if (!__any(todo)) return;
     }
     const int64_t kb = uniform(k0);                   // of the wave's first chain: the lowest
@@ -566,12 +591,7 @@ __global__ __launch_bounds__(64) void k_chain_smoother_tv(Args a, int pass) {
         double oP, om;
         load_state(a.end[0], x.e < x.hi ? x.c + 1 : x.c, t, Ps, ms);
         load_state(a.entry, x.c, t, oP, om);
-        const bool same = agree(oP, om, Ps, ms, t) || x.e == x.hi;
-        if (same && x.live) {
-            load_state(a.end[0], x.c, t, oP, om);
-            store_state(a.end[1], x.c, t, oP, om);
-        }
-        todo = todo && !same;
+        todo = again(a, x, oP, om, Ps, ms, a.near, x.e == x.hi, t);
         if (!__any(todo)) return;
     }
     // groups of kAhead steps that end at s exactly: rows below it are never formed
@@ -647,9 +667,9 @@ __global__ __launch_bounds__(64) void k_chain_smoother_tv(Args a, int pass) {
 //          from the columns' inputs A^3 B z_0 + A^2 B z_1 + A B z_2 + B z_3 + c';
 //   O_q    the means of steps q, 4 + q, 8 + q, 12 + q, O_q = A O_{q-1} + B Z_q + c.
 // 14 products for 16 steps, 8 where only the last is wanted.
-// Chains that start in there run the means alone from half as many steps again
-// as the covariances take to settle (the mean forgets at half their rate, and
-// they settle 2^-60 deep); those whose start would fall into the head start
+// Chains that start in there run the means alone from 1 3/4 times the steps that
+// the covariances take to settle (the mean forgets at half their rate, and they
+// settle 2^-60 deep: 2^-52); those whose start would fall into the head start
 // with the sequence.
 // Bound by the slowest head (0.33 us a step of the filter, and as the smoother's
 // tail and head 0.2 and 0.45) beside the rows to write: 8.5 M steps of 1024 CV
@@ -823,7 +843,7 @@ __global__ __launch_bounds__(64) void k_chain_filter_ti(Args a, int pass, int wr
     const double* md = a.model + x.b * kModel + 4 * t.i + t.j;
     const double Pstar = md[48];
     const int head = a.head[2 * x.b];
-    const int64_t warm = (head + head / 2 + kLong - 1) & -kLong;
+    const int64_t warm = (head + head / 2 + head / 4 + kLong - 1) & -kLong;
     int64_t k0 = pass ? x.s : x.s - warm;
     if (pass == 0 && k0 < x.lo + head) k0 = x.lo;
     bool todo = x.live;
@@ -835,12 +855,7 @@ __global__ __launch_bounds__(64) void k_chain_filter_ti(Args a, int pass, int wr
         double oP, om;
         load_state(a.end[0], x.s > x.lo ? x.c - 1 : x.c, t, P, m);
         load_state(a.entry, x.c, t, oP, om);
-        const bool same = agree(oP, om, P, m, t) || x.s == x.lo;
-        if (same && x.live) {
-            load_state(a.end[0], x.c, t, oP, om);
-            store_state(a.end[1], x.c, t, oP, om);
-        }
-        todo = todo && !same;
+        todo = again(a, x, oP, om, P, m, near_of(a.l, head), x.s == x.lo, t);
         if (!__any(todo)) return;
     }
     const double FT = pick(at.nn, a.F[x.b * n2 + at.ft]), Q = pick(at.nn, a.Q[x.b * n2 + at.q]);
@@ -940,7 +955,7 @@ __global__ __launch_bounds__(64) void k_chain_smoother_ti(Args a, int pass, int 
     const double* md = a.model + x.b * kModel + 4 * t.i + t.j;
     const double Pstar = md[48], ETs = md[64], Psstar = md[80];
     const int head = a.head[2 * x.b], tail = a.head[2 * x.b + 1];
-    const int64_t warm = (tail + tail / 2 + kLong - 1) & -kLong;
+    const int64_t warm = (tail + tail / 2 + tail / 4 + kLong - 1) & -kLong;
     int64_t from = pass ? x.e : x.e + warm;          // the step with known moments
     if (from > x.hi - 1 - tail && (pass == 0 || x.e == x.hi)) from = x.hi - 1;
     bool todo = x.live;
@@ -958,12 +973,7 @@ __global__ __launch_bounds__(64) void k_chain_smoother_ti(Args a, int pass, int 
         double oP, om;
         load_state(a.end[0], x.e < x.hi ? x.c + 1 : x.c, t, Ps, ms);
         load_state(a.entry, x.c, t, oP, om);
-        const bool same = agree(oP, om, Ps, ms, t) || x.e == x.hi;
-        if (same && x.live) {
-            load_state(a.end[0], x.c, t, oP, om);
-            store_state(a.end[1], x.c, t, oP, om);
-        }
-        todo = todo && !same;
+        todo = again(a, x, oP, om, Ps, ms, near_of(a.l, tail), x.e == x.hi, t);
         if (!__any(todo)) return;
     }
     const double FT = pick(at.nn, a.F[x.b * n2 + at.ft]), Q = pick(at.nn, a.Q[x.b * n2 + at.q]);
@@ -1123,8 +1133,8 @@ __global__ __launch_bounds__(64) void k_chain_check(Args a) {
     double P, m, P2, m2;
     load_state(a.entry, x.c, t, P, m);
     load_state(a.end[1], edge ? x.c : (SMOOTHER ? x.c + 1 : x.c - 1), t, P2, m2);
-    const bool same = agree(P, m, P2, m2, t);
-    if (x.live && !edge && !same) a.ctl[0] = 0;
+    const bool same = agree(P, m, P2, m2, kSame, t), close = agree(P, m, P2, m2, kRounding, t);
+    if (x.live && !edge && !same && !(close && a.forgets[x.c])) a.ctl[0] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1206,10 +1216,14 @@ bool applies(int nx, int ny, int32_t B, int64_t total, bool mixed, bool tv, bool
 }
 
 bool layout(Args& a, char* base, size_t bytes, bool tv) {
-    // time-varying: CV models of all step sizes in use agree to rounding after 100 to
-    // 180 steps; else the setup knows
-    a.warm = 192;
+    // time-varying: a constant-velocity model sampled at 0.05 to 0.15 s forgets to
+    // rounding in 190 to 210 steps where q / r = 4 s^-3, in 230 where 2.4, 370 where
+    // 0.4, 600 where 0.04: those are met by the second pass, if at all, which starts
+    // a.l + a.warm steps before.  Else the setup knows
+    a.warm = 224;
     a.l = tv ? (a.total + 4095) / 4096 : std::max<int64_t>(64, (a.total + 12287) / 12288);
+    // what has not been forgotten after a.warm steps falls on as it did until then
+    a.near = std::exp2(-2.0 * 50.0 * (double)a.warm / (double)(a.warm + a.l));
     const int group = tv ? kAhead : kLong;            // chains start and end with a group of steps
     a.l = (a.l + group - 1) / group * group;
     a.max_chains = (a.total + a.l - 1) / a.l + (a.offsets ? a.B : 0);
@@ -1222,6 +1236,7 @@ bool layout(Args& a, char* base, size_t bytes, bool tv) {
     a.first = reinterpret_cast<int64_t*>(take(a.B + 1));
     a.sequence = a.offsets ? reinterpret_cast<int*>(take((a.max_chains + 1) / 2)) : nullptr;
     a.model = tv ? nullptr : take((int64_t)a.B * kModel);
+    a.forgets = reinterpret_cast<int*>(take((a.max_chains + 1) / 2));
     a.head = tv ? nullptr : reinterpret_cast<int*>(take(a.B));
     a.entry = take(a.max_chains * kState);
     a.end[0] = take(a.max_chains * kState);

@@ -7,8 +7,8 @@
 // own steps with are compared with those its predecessor ended with.  The first
 // chain of a sequence starts from the prior itself, so where all of them agree
 // to rounding every chain has the sequential filter's values.  Chains that do
-// not agree run once more from the predecessor's end; if one still differs, or
-// a factorisation failed, the flag ctl[0] is cleared and the general scan
+// not agree run once more from the predecessor's end; if one still differs (see
+// kSame in chains.hip), or a factorisation failed, the flag ctl[0] is cleared and the general scan
 // kernels, which follow in the stream and return at once otherwise, do the
 // work.  The smoother does the same backwards.  With one time-invariant model per
 // sequence, covariances that have settled are not run again: there a chain is the
@@ -38,6 +38,8 @@ struct Args {
     int64_t* first;              // [B+1] chains of the sequences before
     int* sequence;               // [chains] a chain's sequence (packed sequences)
     double* model;               // [B][kModel] settled values (time-invariant models)
+    double near;                 // see kSame (time-varying models)
+    int* forgets;                // [chains] the first difference was within `near`
     int* head;                   // [B][2] steps after which P and Ps have settled, in 16 (0: they have not)
     double *entry, *end[2];      // [chains][kState] moments that a chain entered and ended with
 };

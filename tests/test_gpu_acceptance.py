@@ -174,3 +174,60 @@ def test_small_pivots(pks, seed, pivot):
     for k, v in zip(("m", "P", "ms", "Ps"), out):
         err = wl.max_rel_err(v[s:e].cpu().numpy(), ref[k])
         assert err <= TOL["fp64"], (k, err)
+
+
+# ---------------------------------------------------------------------------
+# overlapped chains: a chain that is accepted is the recursion, to its rounding
+# ---------------------------------------------------------------------------
+def extended_filter(rows, y, m, P, steps):
+    """`steps` steps of many windows at once in extended precision (rows, y: [windows, steps, ...])."""
+    F, Q, H, R = rows
+    t = lambda a: np.swapaxes(a, -1, -2)
+    mm = lambda a, b: np.sum(a[..., :, :, None] * b[..., None, :, :], axis=-2)
+    for k in range(steps):
+        m, P = (F[:, k] * m[:, None, :]).sum(-1), mm(mm(F[:, k], P), t(F[:, k])) + Q[:, k]
+        PH = mm(P, t(H[:, k]))
+        S = mm(H[:, k], PH) + R[:, k]
+        det = S[:, 0, 0] * S[:, 1, 1] - S[:, 0, 1] * S[:, 1, 0]
+        Si = np.stack([np.stack([S[:, 1, 1], -S[:, 0, 1]], -1), np.stack([-S[:, 1, 0], S[:, 0, 0]], -1)], -2) / det[:, None, None]
+        K = mm(PH, Si)
+        m = m + (K * (y[:, k] - (H[:, k] * m[:, None, :]).sum(-1))[:, None, :]).sum(-1)
+        P = P - mm(K, t(PH))
+        P = (P + t(P)) / 2
+        yield m, P
+
+
+@pytest.mark.parametrize("q", [1.0, 0.6, 0.5, 0.4])
+@pytest.mark.parametrize("offset", [0.0, 1e6])
+def test_time_varying_filter_to_rounding(pks, q, offset):
+    """Models that forget in about the steps that a chain runs before its own: what
+    they have not forgotten is in the means of each chain's first steps.  Two
+    recursions that have met stay within 2^-51 of each other in the units below
+    (the largest of 17000 samples); eight times that is allowed."""
+    T = 1 << 19
+    rng = np.random.default_rng(17)
+    dts = rng.uniform(0.05, 0.15, size=T)
+    y, _ = wl.simulate_cv_tv(dts, q, 0.25, rng)
+    y = y + offset
+    model = wl.cv_model_tv(dts, q, 0.25)
+    model.m0 = np.array([offset, offset, 0.0, 0.0])
+    m, P, _, _ = pks.filter_smooth(pks.to_device(model, time_varying=True), torch.as_tensor(y).cuda(), "fp64")
+    torch.cuda.synchronize()
+    m, P = m.cpu().numpy(), P.cpu().numpy()
+    # windows that start where the library is already exact to 1e-9, run 800 steps until that is forgotten
+    run, look = 800, 700
+    start = rng.integers(1000, T - run - look, size=200)
+    at = (start[:, None] + 1 + np.arange(run + look)[None]).ravel()
+    ext = lambda a: a[at].reshape((200, run + look) + a.shape[1:]).astype(np.longdouble)
+    rows = [ext(a) for a in (model.F, model.Q, model.H, model.R)]
+    worst = [0.0, 0.0]
+    for k, (mr, Pr) in enumerate(extended_filter(rows, ext(y), m[start].astype(np.longdouble),
+                                                 P[start].astype(np.longdouble), run + look)):
+        if k < run:
+            continue
+        d = np.sqrt(np.diagonal(Pr, axis1=1, axis2=2))
+        size = np.sqrt(1.0 + ((mr / d) ** 2).sum(-1, keepdims=True))
+        dm = np.abs(m[start + 1 + k] - mr) / (d * size)
+        dP = np.abs(P[start + 1 + k] - Pr) / (d[:, :, None] * d[:, None, :])
+        worst = [max(worst[0], float(dm.max())), max(worst[1], float(dP.max()))]
+    assert worst[0] <= 2.0 ** -48 and worst[1] <= 2.0 ** -47, np.log2(worst)
