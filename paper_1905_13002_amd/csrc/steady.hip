@@ -20,8 +20,8 @@ namespace steady {
 
 namespace {
 
-// (M^T)^-1 for M = I + C J given the tiles of C and J: unpivoted, kept when its
-// residual is below 1e-11 in every entry, else with partial pivoting
+// (M^T)^-1 for M = I + C J given the tiles of C and J: unpivoted, refined where the
+// residual is not rounding, with partial pivoting where it is not small
 template <int KX>
 __device__ __forceinline__ f64x4 inv_ijc(const f64x4& C, const f64x4& J, const f64x4& I, double* st, int n, bool& ok) {
     const f64x4 MT = mm<KX>(J, C, I);
@@ -31,7 +31,10 @@ __device__ __forceinline__ f64x4 inv_ijc(const f64x4& C, const f64x4& J, const f
     double dev = 0.0;
 #pragma unroll
     for (int v = 0; v < KX; ++v) dev = fmax(dev, fabs(R[v] - I[v]));
-    if (!good || __any(!(dev <= 1e-11))) NT = inv_piv(MT, n, st, ok);
+    if (!good || __any(!(dev <= kExact))) {
+        if (!good || __any(!(dev <= kSmall))) return inv_piv(MT, n, st, ok);
+        NT = mm<KX>(tr(NT, st), I - R, NT);
+    }
     return NT;
 }
 

@@ -145,7 +145,8 @@ struct Eng {
         const f64x4 d = r == c ? diagonal(y) : zero4(), di = xty(d, ones()), dj = xty(ones(), d);
         return !any(!steady::meets(x, y, di, dj));
     }
-    // (M^T)^-1 for M = I + C J: kept when its residual is below 1e-11 in every entry
+    // (M^T)^-1 for M = I + C J: refined where the residual is not rounding; `ok` is
+    // cleared where it is not small
     __device__ __forceinline__ f64x4 inv_ijc(const f64x4& C, const f64x4& J, bool& ok) const {
         const f64x4 I = id();
         const f64x4 N = inv<false>(xty(J, C, I), ok);
@@ -153,8 +154,9 @@ struct Eng {
         double dev = 0.0;
 #pragma unroll
         for (int v = 0; v < 4; ++v) dev = fmax(dev, fabs(R[v] - I[v]));
-        ok = ok && !any(!(dev <= 1e-11));
-        return N;
+        if (!any(!(dev <= kExact))) return N;
+        ok = ok && !any(!(dev <= kSmall));
+        return xty(tr(N), I - R, N);
     }
 };
 

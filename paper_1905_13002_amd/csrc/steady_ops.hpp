@@ -19,6 +19,11 @@ using namespace w16;
 // one (checked when the head is formed)
 constexpr double kTiny = 8.673617379884035e-19;      // 2^-60
 constexpr double kSpare = 128.0;
+// Residuals, in every entry, of an inverse formed without row exchanges: rounding
+// (1e-15 where no pivot is small), and what one Newton step still brings there.  (Kept
+// as it was at a residual of 1e-11, the settled covariance of a model with a pivot
+// of 1e-3 was 1.7e-13 off; 7e-16 after the step.)
+constexpr double kExact = 1e-14, kSmall = 1e-8;
 // and how far the last covariance of the head (the tail), which is formed step by
 // step, may be from the settled one, which is doubled: two digits inside the parity bar
 constexpr double kMeet = 1e-11;

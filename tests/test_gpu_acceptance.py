@@ -176,6 +176,42 @@ def test_small_pivots(pks, seed, pivot):
         assert err <= TOL["fp64"], (k, err)
 
 
+def settled_by_doubling(model):
+    """The settled filtered covariance in extended precision (pivoted inverses, two Newton steps)."""
+    F, Q, H, R = (np.asarray(a, dtype=np.longdouble) for a in (model.F, model.Q, model.H, model.R))
+
+    def inv(M):
+        I = np.eye(len(M), dtype=np.longdouble)
+        X = np.linalg.inv(M.astype(np.float64)).astype(np.longdouble)
+        for _ in range(3):
+            X = X + X @ (I - M @ X)
+        return X
+
+    S = H @ Q @ H.T + R
+    K = Q @ H.T @ inv(S)
+    A, C, J = F - K @ H @ F, Q - K @ S @ K.T, F.T @ H.T @ inv(S) @ H @ F
+    for _ in range(9):
+        X = inv(np.eye(len(F), dtype=np.longdouble) + C @ J)
+        A, C, J = A @ X @ A, A @ X @ C @ A.T + C, A.T @ J @ X @ A + J
+    return C
+
+
+@pytest.mark.parametrize("seed", [65, 222, 370])
+@pytest.mark.parametrize("pivot", [1e-3, 3e-5, 1e-6])
+def test_small_pivots_one_model(pks, seed, pivot):
+    """An inverse without row exchanges loses |log10 pivot| digits; the settled
+    covariance is still to have those that the model gives it (the sequential
+    recursion: 1e-15): 1e-13 is a few hundred roundings."""
+    T, model = 250000, small_pivot_model(seed, pivot)
+    y = np.random.default_rng(seed).standard_normal((T, 2))
+    ws = pks.workspace(4, 2, T, 1, "fp64")
+    _, P, _, _ = pks.filter_smooth(pks.to_device(model), torch.as_tensor(y).cuda(), "fp64", ws=ws)
+    torch.cuda.synchronize()
+    C = settled_by_doubling(model)
+    err = np.max(np.abs(P[T // 2].cpu().numpy() - C)) / np.max(np.abs(C))
+    assert err <= 1e-13, float(err)
+
+
 # ---------------------------------------------------------------------------
 # overlapped chains: a chain that is accepted is the recursion, to its rounding
 # ---------------------------------------------------------------------------
