@@ -160,6 +160,15 @@ struct Eng {
     }
 };
 
+// A word that other workgroups of the launch may clear meanwhile: the same value in
+// every wave of this one, which meet at barriers behind it
+__device__ __forceinline__ int read_once(const int* p) {
+    __shared__ int v;
+    if (threadIdx.x == 0) v = *p;
+    __syncthreads();
+    return v;
+}
+
 template <int NT>
 struct ModelL {
     f64x4 F, FT, Q, HT, R;
@@ -260,7 +269,7 @@ __global__ __launch_bounds__(256) void k_stl_probe(Args a) {
 template <typename R>
 __global__ __launch_bounds__(256) void k_stl_check(Args a) {
     extern __shared__ __align__(16) double dyn[];
-    const int nh = a.ctl[0];
+    const int nh = read_once(a.ctl);
     if (nh == 0) return;
     if (rows_differ<R>(a, nh, blockIdx.x, gridDim.x, reinterpret_cast<R*>(dyn))) a.ctl[0] = 0;
 }
@@ -384,7 +393,7 @@ __global__ __launch_bounds__(64 * NT * NT) void k_stl_double(Args a) {
 template <int NT>
 __global__ __launch_bounds__(64 * NT * NT) void k_stl_tables(Args a) {
     extern __shared__ __align__(16) double lds[];
-    const int nh = a.ctl[0];
+    const int nh = read_once(a.ctl);
     if (nh == 0) return;
     const Eng<NT> e(lds, a);
     const int nrun = nh / kRun, n = a.nx, n2 = n * n, m = a.ny;
