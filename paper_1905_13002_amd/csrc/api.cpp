@@ -195,7 +195,8 @@ ScanArgs make_scan_args(const pks_model& model, int32_t B, const int64_t* offset
 // Enqueue the requested passes.  passes: 1 = filter, 2 = smoother, 3 = both.
 pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, int64_t total,
                    const void* y, void* m, void* P, void* ms, void* Ps, pks_precision prec,
-                   void* ws, size_t ws_bytes, int passes, const TileConfig* forced, hipStream_t s, bool tv) {
+                   void* ws, size_t ws_bytes, int passes, const TileConfig* forced, hipStream_t s, bool tv,
+                   bool general) {
     const int nmodels = tv ? (int)total : (model.per_sequence ? B : 1);
     const WsLayout L = ws_layout(model.nx, model.ny, total, tv ? nmodels : B, prec);
     if (ws_bytes < L.total)
@@ -216,7 +217,7 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
     // the work.
     hipError_t e;
     const int* skip = nullptr;
-    if (((passes & 1) || model.nx > 16) && !tv && !model.per_sequence &&
+    if (!general && ((passes & 1) || model.nx > 16) && !tv && !model.per_sequence &&
         steady::applies(model.nx, model.ny, B, total, mixed)) {
         char* base = static_cast<char*>(ws);
         steady::Args t{};
@@ -240,7 +241,7 @@ pks_status enqueue(const pks_model& model, int32_t B, const int64_t* offsets, in
     }
     // models that change at every step, or one per sequence: overlapped chains,
     // verified on the device, the same way
-    if ((passes & 1) && (tv || model.per_sequence) &&
+    if (!general && (passes & 1) && (tv || model.per_sequence) &&
         chains::applies(model.nx, model.ny, B, total, mixed, tv, (passes & 2) != 0)) {
         char* base = static_cast<char*>(ws);
         chains::Args t{};

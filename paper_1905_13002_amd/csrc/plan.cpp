@@ -345,7 +345,7 @@ pks_status pks_autotune(int32_t nx, int32_t ny, int32_t B, int64_t total, pks_pr
             for (int r = 0; r < 4 && st == PKS_OK; ++r) {
                 hipEventRecord(e0, s);
                 st = enqueue(model, B, offs, T, buf + off_y, buf + off_m, buf + off_P, buf + off_ms, buf + off_Ps,
-                             prec, buf + off_ws, wsb, 3, &c, s);
+                             prec, buf + off_ws, wsb, 3, &c, s, false, true);
                 hipEventRecord(e1, s);
                 hipEventSynchronize(e1);
                 float ms = 0.f;
