@@ -92,9 +92,15 @@ bool write_cache(const char* path, const std::map<std::string, TileConfig>& m) {
     return std::rename(tmp.c_str(), path) == 0;
 }
 
-bool valid_config(const TileConfig& c, int nx) {
+// one and two steps a thread: nx = 3, 4 only, and no more threads than a workspace for
+// `total` steps holds
+bool short_fits(int ept, int nx, int64_t total) {
+    return (nx == 3 || nx == 4) && (ept == 1 || ept == 2) && (total + ept - 1) / ept <= small_threads(nx, total);
+}
+
+bool valid_config(const TileConfig& c, int nx, int64_t total) {
     if (!small_supported(nx)) return c.blocks >= 1;
-    return (c.ept == 4 || c.ept == 8 || c.ept == 16) && (c.ept1 == 0 || c.ept1 == 1 || c.ept1 == 2 || c.ept1 == 4 || c.ept1 == 8);
+    return (c.ept == 4 || c.ept == 8 || c.ept == 16 || short_fits(c.ept, nx, total)) && (c.ept1 == 0 || c.ept1 == 1 || c.ept1 == 2 || c.ept1 == 4 || c.ept1 == 8);
 }
 
 struct Plan {
@@ -110,7 +116,7 @@ TileConfig tuned_config(int nx, int ny, int32_t B, int64_t total, pks_precision 
     if (p) {
         auto m = read_cache(p);
         auto it = m.find(cache_key(nx, ny, B, total, prec));
-        if (it != m.end() && valid_config(it->second, nx)) return it->second;
+        if (it != m.end() && valid_config(it->second, nx, total)) return it->second;
     }
     return small_default_config(nx, total, prec == PKS_MIXED_FP32);
 }
@@ -316,13 +322,17 @@ pks_status pks_autotune(int32_t nx, int32_t ny, int32_t B, int64_t total, pks_pr
     // fewer workgroups in flight)
     std::vector<TileConfig> cands;
     if (small_supported(nx)) {
-        const int epts[3] = {4, 8, 16};
+        // (an entry serves every length of its power of two: one and two steps a thread
+        // where the longest of them fits)
+        const int64_t longest = ((int64_t)2 << ilog2(T)) - 1;
+        const int epts[5] = {1, 2, 4, 8, 16};
         const int ept1s[5] = {0, 1, 2, 4, 8};
-        for (int ei = 0; ei < 3; ++ei)
+        for (int ei = 0; ei < 5; ++ei)
             for (int li = 0; li < 5; ++li) {
                 TileConfig c;
                 c.ept = epts[ei];
                 c.ept1 = ept1s[li];
+                if (c.ept < 4 && !short_fits(c.ept, nx, longest)) continue;
                 const int64_t waves = (T + 64 * c.ept - 1) / (64 * c.ept);
                 if (c.ept1 == 0 && waves > (int64_t)64 * 256) continue;    // top level would be too long
                 if (c.ept1 != 0 && waves < 128) continue;                  // second level not useful
