@@ -491,6 +491,15 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_down(HmmArgs a, const doubl
 // smoother at K = 64, T = 65536: 411 us, by the block-element scan 2460 us.
 // ---------------------------------------------------------------------------
 constexpr int kWarm = 448, kRepairs = 3, kAhead = 4;
+// Chains that do not forget (permutations, states that stay for hundreds of steps
+// and look alike) are given up early: the wave whose block starts the sequence, and
+// has no warm-up of its own, runs two starts with no state in common for kPilotSteps
+// steps at up to three places, and where two of the pairs are still kApart apart (L1;
+// 2 at the start, 0.07 left of a chain that stays in its states for ten steps) a
+// flag stops the others.  A permutation of 16 states, 2^16 steps: 353 us, by the scan
+// alone 294 (535 with the whole attempt before it); of 64, 4096 steps: 518, 455 (685).
+constexpr int kPilots = 3, kPilotSteps = 32;
+constexpr double kApart = 0.7;
 constexpr double kSame = 1.4210854715202004e-14;      // 2^-46
 // Sums and predictions below the normal range: the reciprocal overflows where the
 // quotient it stands for does not.  Such a block is not accepted.
@@ -671,6 +680,81 @@ __global__ __launch_bounds__(256) void k_hmm_scaled(OverArgs o) {
     }
 }
 
+// the flag that an attempt (0: the filter's, 1: the smoother's) has failed
+__device__ __forceinline__ int failed(const OverArgs& o, int smoother) {
+    return __hip_atomic_load(o.ctl + 2 + smoother, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// steps of the warm-up between two looks at it (two pilots take about 110; a look in
+// the steps' own loop, even a rare one, keeps their loads from running ahead)
+constexpr int kLook = 128;
+// runs the pilots: apart(k) the distance of the two starts of step k on
+template <typename F>
+__device__ __forceinline__ void pilots(const OverArgs& o, int smoother, F&& apart) {
+    int votes = 0;
+#pragma unroll 1
+    for (int i = 1; i <= kPilots; ++i) {
+        votes += apart((o.h.T - 2 * kPilotSteps) * i / (kPilots + 1) + kPilotSteps) > kApart;
+        if (votes == 2) {
+            if (threadIdx.x == 0) atomicAdd(o.ctl + 2 + smoother, 1);
+            return;
+        }
+    }
+}
+
+// two starts, the even states and the odd ones, from step k on
+template <int KV>
+__device__ __forceinline__ double pilot(const HmmArgs& a, const MatVec<KV, false>& mv, int64_t k, int lane) {
+    const int K = a.K, x = lane & (KV - 1), col = x < K ? x : K - 1;
+    double v[2] = {x < K && !(x & 1) ? 1.0 : 0.0, x < K && (x & 1) ? 1.0 : 0.0};
+    auto scale = [&] {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) v[q] *= recip(all_sum(v[q]) * (KV / 64.0));
+    };
+#pragma unroll 1
+    for (int i = 0; i < kPilotSteps; i += kAhead) {
+        double w[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) w[j] = a.alpha[(k + i + j) * K + col];
+        scale();
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            double y[2];
+            mv(v, y, lane);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) v[q] = x < K ? y[q] * w[j] : 0.0;
+        }
+    }
+    scale();
+    return all_sum(fabs(v[0] - v[1])) * (KV / 64.0);
+}
+// and backwards, from the filtered distribution of step k on
+template <int KV>
+__device__ __forceinline__ double pilot_back(const HmmArgs& a, const MatVec<KV, false>& bwd, int64_t k, int lane) {
+    const int K = a.K, x = lane & (KV - 1), col = x < K ? x : K - 1;
+    const double al = x < K ? a.alpha[k * K + col] : 0.0;
+    double g[2] = {x & 1 ? 0.0 : al, x & 1 ? al : 0.0};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) g[q] *= recip(all_sum(g[q]) * (KV / 64.0));
+#pragma unroll 1
+    for (int i = 1; i <= kPilotSteps; i += kAhead) {
+        double av[kAhead], iv[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            av[j] = a.alpha[(k - i - j) * K + col];
+            iv[j] = a.gamma[(k - i - j) * K + col];
+        }
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const double v[2] = {g[0] * iv[j], g[1] * iv[j]};
+            double y[2];
+            bwd(v, y, lane);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) g[q] = x < K ? y[q] * av[j] : 0.0;
+        }
+    }
+    return all_sum(fabs(g[0] - g[1])) * (KV / 64.0);
+}
+
 // The distribution that block b enters with, from kWarm steps before it.
 // kAhead steps at a time, without a branch between them; the loads run two
 // groups ahead.  The vector is scaled once a group, and by the sum that the
@@ -683,10 +767,11 @@ __global__ __launch_bounds__(64) void k_hmm_filter_warm(OverArgs o) {
     const bool live = x < K;
     const int col = live ? x : K - 1;                 // lanes without a state: the last one's loads, times zero
     const double mask = live ? 1.0 : 0.0;
-    int64_t k = s > kWarm ? s - kWarm : 0;
-    double al = live ? (k == 0 ? a.p0[x] : 1.0 / K) : 0.0, r = mask;
     MatVec<KV, false> mv;
     mv.load(a.Pi, K, false, lane, nullptr);
+    if (b == 0) pilots(o, 0, [&](int64_t at) { return pilot<KV>(a, mv, at, lane); });
+    int64_t k = s > kWarm ? s - kWarm : 0;
+    double al = live ? (k == 0 ? a.p0[x] : 1.0 / K) : 0.0, r = mask;
     double w[kAhead], raw[kAhead];
     auto fetch = [&](int64_t kk, double (&v)[kAhead]) {
 #pragma unroll
@@ -695,23 +780,26 @@ __global__ __launch_bounds__(64) void k_hmm_filter_warm(OverArgs o) {
     fetch(k, w);
     fetch(k + kAhead, raw);
     double c = 1.0;
-    for (; k < s; k += kAhead) {
-        double nxt[kAhead];
-        fetch(k + 2 * kAhead, nxt);
-        r = recip(c) * mask;
+    while (k < s) {
+        for (const int64_t stop = min(s, k + kLook); k < stop; k += kAhead) {
+            double nxt[kAhead];
+            fetch(k + 2 * kAhead, nxt);
+            r = recip(c) * mask;
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
-            const double v[1] = {al};
-            double y[1];
-            mv(v, y, lane);
-            al = y[0] * (w[j] * (j == 0 ? r : mask));
-            if (j == 0) c = all_sum(al) * (KV / 64.0);       // every state KV / 64 times
-        }
+            for (int j = 0; j < kAhead; ++j) {
+                const double v[1] = {al};
+                double y[1];
+                mv(v, y, lane);
+                al = y[0] * (w[j] * (j == 0 ? r : mask));
+                if (j == 0) c = all_sum(al) * (KV / 64.0);       // every state KV / 64 times
+            }
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
-            w[j] = raw[j];
-            raw[j] = nxt[j];
+            for (int j = 0; j < kAhead; ++j) {
+                w[j] = raw[j];
+                raw[j] = nxt[j];
+            }
         }
+        if (failed(o, 0) != 0) return;
     }
     // block 0 enters with the prior as it is
     o.entry[b * KV + x] = s == 0 ? al : al * recip(all_sum(al) * (KV / 64.0));
@@ -726,6 +814,7 @@ __global__ __launch_bounds__(64) void k_hmm_filter_over(OverArgs o, int pass) {
     const int lane = threadIdx.x, K = a.K, x = lane & (KV - 1);
     const int64_t b = blockIdx.x, s = b * o.l, e = min(s + o.l, a.T);
     const bool live = x < K;
+    if (failed(o, 0) != 0) return;
     const double* in = o.end[(pass + 1) & 1];
     double* out = o.end[pass & 1];
     int64_t k = s;
@@ -735,6 +824,11 @@ __global__ __launch_bounds__(64) void k_hmm_filter_over(OverArgs o, int pass) {
         al = b > 0 ? in[(b - 1) * KV + x] : 0.0;
         if (b == 0 || same_dist(was, al, live)) {
             out[b * KV + x] = own;
+            return;
+        }
+        // ten bits in kWarm steps: the others will not come in the repairs'
+        if (pass == 1 && o.l < kWarm && all_sum(fabs(was - al)) * (KV / 64.0) > 1e-3) {
+            if (lane == 0) atomicAdd(o.ctl + 2, 1);
             return;
         }
         o.entry[b * KV + x] = al;
@@ -859,14 +953,14 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_warm(OverArgs o) {
     if (o.need ? *o.need == 0 : false) return;
     const int lane = threadIdx.x, K = a.K, x = lane & (KV - 1);
     const int64_t b = blockIdx.x, e = min((b + 1) * o.l, a.T);
-    if (e == a.T) return;
     const bool live = x < K;
     const int col = live ? x : K - 1;
     const double mask = live ? 1.0 : 0.0;
-    const int64_t from = min(e + kWarm, a.T - 1);
-    double g = a.alpha[from * K + col] * mask;
     MatVec<KV, false> bwd;
     bwd.load(a.Pi, K, true, lane, nullptr);
+    if (e == a.T) return pilots(o, 1, [&](int64_t at) { return pilot_back<KV>(a, bwd, at, lane); });
+    const int64_t from = min(e + kWarm, a.T - 1);
+    double g = a.alpha[from * K + col] * mask;
     double av[kAhead], iv[kAhead], ra[kAhead], ri[kAhead];
     auto fetch = [&](int64_t kk, double (&u)[kAhead], double (&v)[kAhead]) {
 #pragma unroll
@@ -879,23 +973,26 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_warm(OverArgs o) {
     int64_t k = from - 1;
     fetch(k, av, iv);
     fetch(k - kAhead, ra, ri);
-    for (; k >= e; k -= kAhead) {
-        double na[kAhead], ni[kAhead];
-        fetch(k - 2 * kAhead, na, ni);
+    while (k >= e) {
+        for (const int64_t stop = max(e, k - kLook + 1); k >= stop; k -= kAhead) {
+            double na[kAhead], ni[kAhead];
+            fetch(k - 2 * kAhead, na, ni);
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
-            const double v[1] = {g * iv[j]};
-            double y[1];
-            bwd(v, y, lane);
-            g = k - j >= e ? y[0] * (av[j] * mask) : g;
-        }
+            for (int j = 0; j < kAhead; ++j) {
+                const double v[1] = {g * iv[j]};
+                double y[1];
+                bwd(v, y, lane);
+                g = k - j >= e ? y[0] * (av[j] * mask) : g;
+            }
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
-            av[j] = ra[j];
-            iv[j] = ri[j];
-            ra[j] = na[j];
-            ri[j] = ni[j];
+            for (int j = 0; j < kAhead; ++j) {
+                av[j] = ra[j];
+                iv[j] = ri[j];
+                ra[j] = na[j];
+                ri[j] = ni[j];
+            }
         }
+        if (failed(o, 1) != 0) return;
     }
     o.entry[b * KV + x] = g;
 }
@@ -909,6 +1006,7 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_over(OverArgs o, int pass) 
     const int lane = threadIdx.x, K = a.K, x = lane & (KV - 1);
     const int64_t b = blockIdx.x, s = b * o.l, e = min(s + o.l, a.T);
     const bool live = x < K;
+    if (failed(o, 1) != 0) return;
     const double* in = o.end[(pass + 1) & 1];
     double* out = o.end[pass & 1];
     int64_t k = e - 1;       // the step that is formed next
@@ -924,8 +1022,13 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_over(OverArgs o, int pass) 
     } else {
         const double own = in[b * KV + x];
         g = b + 1 < o.nblk ? in[(b + 1) * KV + x] : 0.0;
-        if (b + 1 == o.nblk || same_dist(o.entry[b * KV + x], g, live)) {
+        const double was = o.entry[b * KV + x];
+        if (b + 1 == o.nblk || same_dist(was, g, live)) {
             out[b * KV + x] = own;
+            return;
+        }
+        if (pass == 1 && o.l < kWarm && all_sum(fabs(was - g)) * (KV / 64.0) > 1e-3) {
+            if (lane == 0) atomicAdd(o.ctl + 3, 1);
             return;
         }
         o.entry[b * KV + x] = g;
@@ -999,6 +1102,7 @@ __global__ __launch_bounds__(64) void k_hmm_over_check(OverArgs o) {
     const int lane = threadIdx.x, x = lane & (KV - 1);
     const int64_t b = blockIdx.x, p = FILTER ? b - 1 : b + 1;
     if (!FILTER && o.need && *o.need == 0) return;
+    if (failed(o, !FILTER) != 0) return;
     if (FILTER && lane == 0 && !(fabs(o.blog[b]) < INFINITY)) atomicAdd(&o.ctl[2], 1);
     // (the first block's end is compared with nothing)
     if (!FILTER && b == 0 && __any(!(fabs(o.end[kRepairs & 1][x]) < INFINITY)) && lane == 0) atomicAdd(&o.ctl[3], 1);
