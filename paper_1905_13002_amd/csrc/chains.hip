@@ -27,6 +27,9 @@ constexpr int kAhead = 4;            // steps of a group; their loads are issued
 // then kRounding is enough where the first difference, `near`, says that what was
 // not forgotten by then is by now (below 2^-50).
 constexpr double kSame = 0x1p-98, kRounding = 0x1p-88;
+// The attempt ends where a first difference is 2^8 above `near`: such a chain does not
+// come down to kSame in the second pass either
+constexpr double kHopeless = 0x1p16;
 constexpr double kTiny = 8.673617379884035e-19;       // 2^-60
 constexpr double kMeet = 1e-11;      // how far a head's last covariance, formed step by step, may be from the doubled one
 constexpr int kMaxLog = 9;           // settled after at most 2^kMaxLog steps
@@ -289,7 +292,12 @@ __device__ __forceinline__ void store_state(double* p, int64_t c, const Lane& t,
 __device__ __forceinline__ bool again(const Args& a, const Chain& x, double P, double m, double P2, double m2, double near,
                                       bool edge, const Lane& t) {
     const bool same = agree(P, m, P2, m2, kSame, t), close = agree(P, m, P2, m2, near, t);
+    const bool hopeless = x.live && !edge && !agree(P, m, P2, m2, near * kHopeless, t);
     if (x.live && t.i == 0 && t.j == 0) a.forgets[x.c] = close;
+    if (__any(hopeless)) {
+        if (hopeless) a.ctl[0] = 0;
+        return false;
+    }
     if (x.live && (same || edge)) {
         load_state(a.end[0], x.c, t, P, m);
         store_state(a.end[1], x.c, t, P, m);
@@ -308,18 +316,18 @@ __device__ __forceinline__ double near_of(int64_t l, int head) {
 // sequence fills: two sequences of 800 k steps with a model each, 209 us in all,
 // 347 with a thread a sequence.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ void set_flags(const Args& a) {
+    if (a.reset || a.status[1] != kStatusMagic) {
+        a.status[0] = kStatusOk;
+        a.status[1] = kStatusMagic;
+    }
+    a.ctl[0] = 1;
+}
 __global__ __launch_bounds__(1024) void k_chain_setup(Args a) {
     __shared__ int64_t part[16], starts[1024];
     __shared__ int counts[1024];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (tid == 0) {
-        if (a.reset || a.status[1] != kStatusMagic) {
-            a.status[0] = kStatusOk;
-            a.status[1] = kStatusMagic;
-        }
-        a.ctl[0] = 1;
-    }
-    if (!a.offsets) return;
+    if (tid == 0) set_flags(a);
     int64_t before = 0;
     for (int b0 = 0; b0 < a.B; b0 += 1024) {
         const int b = b0 + tid;
@@ -477,6 +485,72 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
 }
 
 // ---------------------------------------------------------------------------
+// Whether a time-varying model forgets in time: the chains' passes are 0.33 us a
+// step whether they are used or not.  kPilots waves follow at four places each what
+// is left of a start (D, the product of the steps' (I - K H) F: a mean's error in
+// standard deviations) for kPilotSteps steps, and note where the bits lost after half
+// of them and all of them, carried on to the end of the second pass, are fewer than
+// kNeed; two such notes end the attempt.  CV models, q / r from 40 to 0.0004 s^-3,
+// carried on to 288 and 480 steps: within 5 bits of what is lost there up to 60 bits.
+// 13 us before a pass of 265 (2^18 steps) to 470 (2^20); a model that does not
+// forget: 2^18 steps 387 us, by the general scan alone 364, with the whole attempt
+// before it 529.
+// ---------------------------------------------------------------------------
+constexpr int kPilots = 3, kPilotSteps = 48, kNote = 4;       // (notes: from word kNote of the flags)
+constexpr double kNeed = 46.0;
+__device__ __forceinline__ bool given_up(const Args& a) { return a.ctl[kNote] + a.ctl[kNote + 1] + a.ctl[kNote + 2] > 1; }
+
+template <int NY>
+__global__ __launch_bounds__(64) void k_chain_pilot(Args a) {
+    if (blockIdx.x == kPilots) {                      // one sequence: the flags (k_chain_setup otherwise)
+        if (threadIdx.x == 0) set_flags(a);
+        return;
+    }
+    const Lane t = lane_of();
+    const At at = at_of(t, a.nx, a.ny);
+    const int64_t kb = a.total * (blockIdx.x + 1) / (kPilots + 1), k0 = kb + t.b * kPilotSteps;
+    Rows<double> rFT, rQ, rHT, rR;
+    rFT.open(a.F, a.nx * a.nx, a.total, kb, k0, at.nn, at.ft);
+    rQ.open(a.Q, a.nx * a.nx, a.total, kb, k0, at.nn, at.q);
+    rHT.open(a.H, a.nx * a.ny, a.total, kb, k0, at.mn, at.ht);
+    rR.open(a.R, a.ny * a.ny, a.total, kb, k0, at.mm, at.r);
+    Row cur[kAhead], nxt[kAhead];
+    auto fetch = [&](Row (&r)[kAhead]) {
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) r[q] = Row{rFT.get(q), rQ.get(q), rHT.get(q), rR.get(q), 0.0, 0.0};
+        rFT.move(kAhead);
+        rQ.move(kAhead);
+        rHT.move(kAhead);
+        rR.move(kAhead);
+    };
+    double P = pick(at.nn, a.P0[at.q]), D = t.i == t.j ? sqrt(P) : 0.0;
+    auto bits = [&] {
+        const double di = mm(t.i == t.j ? P : 0.0, 1.0);
+        double q = D != 0.0 ? D * D / di : 0.0;
+#pragma unroll
+        for (int s = 1; s < 64; s = s == 2 ? 16 : 2 * s) q = fmax(q, __shfl_xor(q, s, 64));
+        return -0.5 * log2(q);
+    };
+    double half = 0.0;
+    fetch(cur);
+#pragma unroll 1
+    for (int k = 0; k < kPilotSteps; k += kAhead) {
+        if (k == kPilotSteps / 2) half = bits();
+        fetch(nxt);
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            bool fine = true;
+            filter_step<NY>(cur[q], t, D, P, fine);
+            cur[q] = nxt[q];
+        }
+    }
+    const double all = bits();
+    const double lost = all + (all - half) * (double)(a.warm + a.l - kPilotSteps) / (kPilotSteps / 2);
+    const unsigned long long few = __ballot(lost < kNeed && t.i == 0 && t.j == 0);
+    if (threadIdx.x == 0) a.ctl[kNote + blockIdx.x] = __popcll(few) > 2;
+}
+
+// ---------------------------------------------------------------------------
 // The chains.  Bound by the rows of the model (F, Q, H, R: 368 bytes a step at
 // nx = 4, ny = 2 with y), which the warm-up reads again, and by the latency of a
 // step (six dependent products and the inverse of S: 0.33 us): 4096 chains, a
@@ -486,7 +560,10 @@ __global__ __launch_bounds__(64) void k_chain_models(Args a) {
 // ---------------------------------------------------------------------------
 template <typename T, int NY>
 __global__ __launch_bounds__(64) void k_chain_filter_tv(Args a, int pass) {
-    if (pass && a.ctl[0] == 0) return;
+    if (pass ? a.ctl[0] == 0 : given_up(a)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[0] = 0;
+        return;
+    }
     const Lane t = lane_of();
     const Chain x = chain_of(a, (int64_t)blockIdx.x * 4 + t.b);
     const At at = at_of(t, a.nx, a.ny);
@@ -1151,8 +1228,11 @@ template <typename T, int NX, int NY>
 hipError_t run(const Args& a, bool tv, hipStream_t s) {
     const int writers = kWriters;
     const dim3 grid((unsigned)((a.max_chains + 3) / 4)), more(grid.x + writers), wave(64);
-    timed("k_chain_setup", s, [&] { hipLaunchKernelGGL(k_chain_setup, dim3(1), dim3(a.offsets ? 1024 : 64), 0, s, a); });
-    if (!tv)
+    if (a.offsets) timed("k_chain_setup", s, [&] { hipLaunchKernelGGL(k_chain_setup, dim3(1), dim3(1024), 0, s, a); });
+    if (tv)
+        timed("k_chain_pilot", s,
+              [&] { hipLaunchKernelGGL((k_chain_pilot<NY>), dim3(kPilots + (a.offsets ? 0 : 1)), wave, 0, s, a); });
+    else
         timed("k_chain_models", s,
               [&] { hipLaunchKernelGGL((k_chain_models<NX, NY>), dim3((a.B + 3) / 4), wave, 0, s, a); });
     for (int pass = 0; pass < 2; ++pass)

@@ -33,7 +33,7 @@ struct Args {
     const void* y;
     void *m, *P, *ms, *Ps;
     int* status;
-    int* ctl;                    // [0] 1: this path has done the work
+    int* ctl;                    // [0] 1: this path has done the work; [4], [5], [6] notes of the pilots
     int64_t l, warm, max_chains;
     int64_t* first;              // [B+1] chains of the sequences before
     int* sequence;               // [chains] a chain's sequence (packed sequences)
