@@ -270,7 +270,9 @@ __device__ __forceinline__ void smoother_gain(double FT, double Q, double u, dou
     const double FP = mm(FT, P);
     mp = mm(FT, m, u);
     Pp = mm(FT, mm(P, FT), Q);
-    ET = mm(inv<NX>(Pp, t, ok), FP);
+    // (refined once: a product with an inverse alone loses the digits of Pp's condition)
+    const double Pi = inv<NX>(Pp, t, ok), q = mm(Pi, FP);
+    ET = mm(Pi, FP - mm(Pp, q), q);
 }
 __device__ __forceinline__ void smoother_step(double ET, double Pp, double mp, double m, double P, double& ms, double& Ps) {
     const double U = mm(Ps - Pp, ET);

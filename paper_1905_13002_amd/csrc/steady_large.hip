@@ -132,6 +132,11 @@ struct Eng {
         ok = ok && !any(!good);
         return a;
     }
+    // S^-1 X given the inverse Si of the symmetric S, refined once (as in steady.hip)
+    __device__ __forceinline__ f64x4 solve(const f64x4& S, const f64x4& Si, const f64x4& X) const {
+        const f64x4 q = xty(Si, X);
+        return xty(Si, X - xty(S, q), q);
+    }
     // E L E^T + add, E by its transpose
     __device__ __forceinline__ f64x4 ele(const f64x4& ET, const f64x4& L, const f64x4& add) const {
         return symt(xty(xty(L, ET), ET), add);
@@ -193,7 +198,7 @@ __device__ __forceinline__ void update(const Eng<NT>& e, const ModelL<NT>& x, co
                                        f64x4& Phi) {
     const f64x4 HP = e.xty(x.HT, Pm);
     const f64x4 S = e.symt(e.xty(x.HT, e.tr(HP), x.R), zero4());
-    Kt = e.xty(e.template inv<true>(S, ok), HP);
+    Kt = e.solve(S, e.template inv<true>(S, ok), HP);
     const f64x4 nKt = -Kt;
     P = e.pad(e.symt(e.xty(nKt, HP, Pm), zero4()), e.n, 0.0);
     Phi = e.xty(nKt, e.xty(x.HT, x.F), x.F);
@@ -201,7 +206,7 @@ __device__ __forceinline__ void update(const Eng<NT>& e, const ModelL<NT>& x, co
 template <int NT>
 __device__ __forceinline__ void smooth_elem(const Eng<NT>& e, const f64x4& P, const f64x4& FP, const f64x4& Pm, bool& ok,
                                             f64x4& ET, f64x4& L) {
-    ET = e.xty(e.template inv<true>(Pm, ok), FP);
+    ET = e.solve(Pm, e.template inv<true>(Pm, ok), FP);
     const f64x4 EFP = e.xty(ET, FP), EFPt = e.tr(EFP);
 #pragma unroll
     for (int v = 0; v < 4; ++v) L[v] = P[v] - 0.5 * (EFP[v] + EFPt[v]);

@@ -212,6 +212,61 @@ def test_small_pivots_one_model(pks, seed, pivot):
     assert err <= 1e-13, float(err)
 
 
+def extended_inverse(M):
+    I = np.eye(len(M), dtype=np.longdouble)
+    X = np.linalg.inv(M.astype(np.float64)).astype(np.longdouble)
+    for _ in range(3):
+        X = X + X @ (I - M @ X)
+    return X
+
+
+def extended_moments(model, y, steps, keep):
+    """Filter and smoother in extended precision over `steps` steps; the first `keep`
+    (the smoother starts from the filter's moments behind them, long forgotten by then)."""
+    F, Q, H, R, m, P = (np.asarray(a, dtype=np.longdouble) for a in (model.F, model.Q, model.H, model.R, model.m0, model.P0))
+    u = np.zeros(len(m)) if model.u is None else model.u
+    d = np.zeros(len(H)) if model.d is None else model.d
+    ms, Ps = [], []
+    for k in range(steps):
+        m, P = F @ m + u, F @ P @ F.T + Q
+        K = P @ H.T @ extended_inverse(H @ P @ H.T + R)
+        G = np.eye(len(m), dtype=np.longdouble) - K @ H
+        m, P = m + K @ (y[k] - d - H @ m), G @ P @ G.T + K @ R @ K.T
+        ms.append(m)
+        Ps.append(P)
+    s, S = [ms[-1]], [Ps[-1]]
+    for k in range(steps - 2, -1, -1):
+        Pp = F @ Ps[k] @ F.T + Q
+        E = Ps[k] @ F.T @ extended_inverse(Pp)
+        s.append(ms[k] + E @ (s[-1] - F @ ms[k] - u))
+        S.append(Ps[k] + E @ (S[-1] - Pp) @ E.T)
+    return [np.array(a[:keep]) for a in (ms, Ps, s[::-1], S[::-1])]
+
+
+@pytest.mark.parametrize("nx,ny,T", [(4, 2, 250000), (6, 3, 9000), (20, 7, 9000)])
+@pytest.mark.parametrize("P0", [1e3, 1e4])
+def test_priors_far_above_the_settled_covariance(pks, nx, ny, T, P0):
+    """The tables of the head, from priors at which the oracle's own update loses
+    digits: every entry against extended precision, in standard deviations.  (The
+    first smoothed covariance is what is left of the prior's size: at 1e6 I the general
+    scan's is 1e-7 off, past the parity bar.)"""
+    rng = np.random.default_rng(31 * nx)
+    model = wl.random_stable_model(nx, ny, rng, radius=0.9, with_offsets=True)
+    model = wl.Model(model.F, model.Q, model.H, model.R, model.m0, P0 * np.eye(nx), model.u, model.d)
+    y = wl.single_sequence(model, T, seed=8).y
+    ws = pks.workspace(nx, ny, T, 1, "fp64")
+    out = pks.filter_smooth(pks.to_device(model), torch.as_tensor(y).cuda(), "fp64", ws=ws)
+    torch.cuda.synchronize()
+    assert int(ws[:256].cpu().numpy().view(np.int32)[CTL]) > 0
+    keep = 600
+    m, P, ms, Ps = extended_moments(model, y, 1000, keep)
+    for x, X, means, cov in ((out[0], out[1], m, P), (out[2], out[3], ms, Ps)):
+        d = np.sqrt(np.diagonal(cov, axis1=1, axis2=2))
+        size = np.sqrt(1.0 + ((means / d) ** 2).sum(-1, keepdims=True))
+        assert np.max(np.abs(x[:keep].cpu().numpy() - means) / (d * size)) <= 1e-9
+        assert np.max(np.abs(X[:keep].cpu().numpy() - cov) / (d[:, :, None] * d[:, None, :])) <= 1e-9
+
+
 # ---------------------------------------------------------------------------
 # overlapped chains: a chain that is accepted is the recursion, to its rounding
 # ---------------------------------------------------------------------------
@@ -267,3 +322,48 @@ def test_time_varying_filter_to_rounding(pks, q, offset):
         dP = np.abs(P[start + 1 + k] - Pr) / (d[:, :, None] * d[:, None, :])
         worst = [max(worst[0], float(dm.max())), max(worst[1], float(dP.max()))]
     assert worst[0] <= 2.0 ** -48 and worst[1] <= 2.0 ** -47, np.log2(worst)
+
+
+def test_means_of_models_that_do_not_forget(pks):
+    """A constant state seen through large noise (see test_gpu_chains.py for its
+    covariances): the general scan's means."""
+    T = 1 << 18
+    tile = lambda a: np.broadcast_to(a, (T,) + a.shape).copy()
+    model = wl.Model(tile(np.eye(4)), tile(1e-12 * np.eye(4)), tile(np.eye(2, 4)), tile(1e2 * np.eye(2)),
+                     np.array([5.0, -3.0, 2.0, 1.0]), np.eye(4))
+    y = np.array([5.0, -3.0]) + 10.0 * np.random.default_rng(5).standard_normal((T, 2))
+    ws = pks.workspace(4, 2, T, 1, "fp64", time_varying=True)
+    out = pks.filter_smooth(pks.to_device(model, time_varying=True), torch.as_tensor(y).cuda(), "fp64", ws=ws)
+    torch.cuda.synchronize()
+    assert int(ws[:256].cpu().numpy().view(np.int32)[CTL]) == 0
+    ref = oracle.kf_rts_tv(model.F, model.Q, model.H, model.R, model.m0, model.P0, y)
+    for k, v in zip(("m", "P", "ms", "Ps"), out):
+        assert wl.max_rel_err(v.cpu().numpy(), ref[k]) <= TOL["fp64"], k
+
+
+@pytest.mark.parametrize("each", [False, True])
+def test_priors_far_above_chains(pks, each):
+    """The same by the chains, one time-varying sequence and a model per sequence."""
+    n, rng = 500000, np.random.default_rng(3)
+    mo = wl.cv_model(1.0, 0.25)
+    mo = wl.Model(mo.F, mo.Q, mo.H, mo.R, mo.m0, 1e5 * np.eye(4))
+    T = 2 * n if each else 1 << 18
+    y = torch.as_tensor(rng.standard_normal((T, 2)))
+    if each:
+        packed = wl.Model(*(np.stack([getattr(mo, f)] * 2) for f in ("F", "Q", "H", "R", "m0", "P0")))
+        plan = pks.Plan(pks.to_device(packed, per_sequence=True), y.cuda(), torch.as_tensor([0, n, 2 * n]).cuda(), "fp64")
+        out, ws = plan.launch(), plan.ws
+    else:
+        tile = lambda a: np.broadcast_to(a, (T,) + a.shape).copy()
+        model = wl.Model(tile(mo.F), tile(mo.Q), tile(mo.H), tile(mo.R), mo.m0, mo.P0)
+        ws = pks.workspace(4, 2, T, 1, "fp64", time_varying=True)
+        out = pks.filter_smooth(pks.to_device(model, time_varying=True), y.cuda(), "fp64", ws=ws)
+    torch.cuda.synchronize()
+    assert int(ws[:256].cpu().numpy().view(np.int32)[CTL]) > 0
+    keep = 300
+    m, P, ms, Ps = extended_moments(mo, y.numpy(), 900, keep)
+    for x, X, means, cov in ((out[0], out[1], m, P), (out[2], out[3], ms, Ps)):
+        d = np.sqrt(np.diagonal(cov, axis1=1, axis2=2))
+        size = np.sqrt(1.0 + ((means / d) ** 2).sum(-1, keepdims=True))
+        assert np.max(np.abs(x[:keep].cpu().numpy() - means) / (d * size)) <= 1e-9
+        assert np.max(np.abs(X[:keep].cpu().numpy() - cov) / (d[:, :, None] * d[:, None, :])) <= 1e-9
