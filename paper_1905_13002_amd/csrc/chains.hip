@@ -1302,7 +1302,7 @@ bool layout(Args& a, char* base, size_t bytes, bool tv) {
     // rounding in 190 to 210 steps where q / r = 4 s^-3, in 230 where 2.4, 370 where
     // 0.4, 600 where 0.04: those are met by the second pass, if at all, which starts
     // a.l + a.warm steps before.  Else the setup knows
-    a.warm = 224;
+    a.warm = 208;
     a.l = tv ? (a.total + 4095) / 4096 : std::max<int64_t>(64, (a.total + 12287) / 12288);
     // what has not been forgotten after a.warm steps falls on as it did until then
     a.near = std::exp2(-2.0 * 50.0 * (double)a.warm / (double)(a.warm + a.l));
