@@ -27,6 +27,9 @@ constexpr int kAhead = 4;            // steps of a group; their loads are issued
 // then kRounding is enough where the first difference, `near`, says that what was
 // not forgotten by then is by now (below 2^-50).
 constexpr double kSame = 0x1p-98, kRounding = 0x1p-88;
+// Means of settled models, 16 steps a product, have met at 2^-47.5; what they have not
+// forgotten is below 2^-52 of where they started by the setup's count of steps
+constexpr double kSameSettled = 0x1p-94;
 // The attempt ends where a first difference is 2^8 above `near`: such a chain does not
 // come down to kSame in the second pass either
 constexpr double kHopeless = 0x1p16;
@@ -291,9 +294,9 @@ __device__ __forceinline__ void store_state(double* p, int64_t c, const Lane& t,
 
 // The second pass: whether a chain that entered with (P, m) runs again from its
 // neighbour's end (P2, m2); one that does not keeps its own end
-__device__ __forceinline__ bool again(const Args& a, const Chain& x, double P, double m, double P2, double m2, double near,
-                                      bool edge, const Lane& t) {
-    const bool same = agree(P, m, P2, m2, kSame, t), close = agree(P, m, P2, m2, near, t);
+__device__ __forceinline__ bool again(const Args& a, const Chain& x, double P, double m, double P2, double m2, double met,
+                                      double near, bool edge, const Lane& t) {
+    const bool same = agree(P, m, P2, m2, met, t), close = agree(P, m, P2, m2, near, t);
     const bool hopeless = x.live && !edge && !agree(P, m, P2, m2, near * kHopeless, t);
     if (x.live && t.i == 0 && t.j == 0) a.forgets[x.c] = close;
     if (__any(hopeless)) {
@@ -557,7 +560,7 @@ __global__ __launch_bounds__(64) void k_chain_pilot(Args a) {
 // nx = 4, ny = 2 with y), which the warm-up reads again, and by the latency of a
 // step (six dependent products and the inverse of S: 0.33 us): 4096 chains, a
 // wave per SIMD, balance the two.  nx = 4, ny = 2, FP64, 2^20 steps: the filter
-// 208 us (4 TB/s), the smoother 205 us, where the block elements of the general
+// 228 us, the smoother 220 us, where the block elements of the general
 // scan took 464 us for the constants of every step and 760 us for the scans.
 // ---------------------------------------------------------------------------
 template <typename T, int NY>
@@ -581,7 +584,7 @@ __global__ __launch_bounds__(64) void k_chain_filter_tv(Args a, int pass) {
         double oP, om;
         load_state(a.end[0], x.s > x.lo ? x.c - 1 : x.c, t, P, m);
         load_state(a.entry, x.c, t, oP, om);
-        todo = again(a, x, oP, om, P, m, a.near, x.s == x.lo, t);
+        todo = again(a, x, oP, om, P, m, kSame, a.near, x.s == x.lo, t);
         if (!__any(todo)) return;
     }
     const int64_t kb = uniform(k0);                   // of the wave's first chain: the lowest
@@ -670,7 +673,7 @@ __global__ __launch_bounds__(64) void k_chain_smoother_tv(Args a, int pass) {
         double oP, om;
         load_state(a.end[0], x.e < x.hi ? x.c + 1 : x.c, t, Ps, ms);
         load_state(a.entry, x.c, t, oP, om);
-        todo = again(a, x, oP, om, Ps, ms, a.near, x.e == x.hi, t);
+        todo = again(a, x, oP, om, Ps, ms, kSame, a.near, x.e == x.hi, t);
         if (!__any(todo)) return;
     }
     // groups of kAhead steps that end at s exactly: rows below it are never formed
@@ -752,8 +755,8 @@ __global__ __launch_bounds__(64) void k_chain_smoother_tv(Args a, int pass) {
 // with the sequence.
 // Bound by the slowest head (0.33 us a step of the filter, and as the smoother's
 // tail and head 0.2 and 0.45) beside the rows to write: 8.5 M steps of 1024 CV
-// models, mixed: filter 190 us (143 without the settled rows), smoother 310
-// (257); the general scan, 1225 in all.  Loads are eight groups ahead, and
+// models, mixed: filter 193 us, smoother 323; the general scan, 1225 in all.  Loads
+// are eight groups ahead, and
 // results are written a row a lane: in pieces of 16 bytes the filter took 30 us
 // more.
 // ---------------------------------------------------------------------------
@@ -934,7 +937,7 @@ __global__ __launch_bounds__(64) void k_chain_filter_ti(Args a, int pass, int wr
         double oP, om;
         load_state(a.end[0], x.s > x.lo ? x.c - 1 : x.c, t, P, m);
         load_state(a.entry, x.c, t, oP, om);
-        todo = again(a, x, oP, om, P, m, near_of(a.l, head), x.s == x.lo, t);
+        todo = again(a, x, oP, om, P, m, kSameSettled, near_of(a.l, head), x.s == x.lo, t);
         if (!__any(todo)) return;
     }
     const double FT = pick(at.nn, a.F[x.b * n2 + at.ft]), Q = pick(at.nn, a.Q[x.b * n2 + at.q]);
@@ -1052,7 +1055,7 @@ __global__ __launch_bounds__(64) void k_chain_smoother_ti(Args a, int pass, int 
         double oP, om;
         load_state(a.end[0], x.e < x.hi ? x.c + 1 : x.c, t, Ps, ms);
         load_state(a.entry, x.c, t, oP, om);
-        todo = again(a, x, oP, om, Ps, ms, near_of(a.l, tail), x.e == x.hi, t);
+        todo = again(a, x, oP, om, Ps, ms, kSameSettled, near_of(a.l, tail), x.e == x.hi, t);
         if (!__any(todo)) return;
     }
     const double FT = pick(at.nn, a.F[x.b * n2 + at.ft]), Q = pick(at.nn, a.Q[x.b * n2 + at.q]);
@@ -1272,29 +1275,33 @@ hipError_t run_nx(const Args& a, bool tv, hipStream_t s) {
 
 // Time-varying models.  Filter + smoother, general scan and chains, us:
 //                                                   FP64            mixed (FP32 elements)
-//   nx = 4, ny = 2, 2^18 steps                      371, 249        273, 259
-//                   2^19                            677, 305        531, 312
-//   nx = 3, ny = 1, 2^18                            256, 235        192, 241
-//                   2^19                            543, 280        379, 286
-//   nx = 4, ny = 4, 2^18                            459, 331        360, 369
-//   nx = 2, ny = 1, 2^20                            551, 934        465, 860
-// (the chains' time hardly depends on nx, the general scan's does).  Packed
+//   nx = 4, ny = 2, CV, q / r = 4, 2^18 steps       366, 274        273, 259 (an earlier form of the chains)
+//                   2^19                            686, 337        534, 333
+//                   2^20                            1277, 480       1043, 456
+//   nx = 4, ny = 2, a mixture of models, 2^18       375, 302
+//                   2^19                            684, 389        535, 390
+//   nx = 3, ny = 1, 2^18                            258, 262        192, 241 (as above)
+//                   2^19                            540, 310        394, 315
+//   nx = 4, ny = 4, 2^18                            462, 417        360, 369 (as above)
+//                   2^19                            869, 536        669, 543
+//   nx = 2, ny = 1, 2^20                            551, 934        465, 860 (as above)
+// (the chains' time hardly depends on nx, the general scan's does).  A model that the
+// pilots give up costs 23 us more than the general scan alone, one that they let by
+// and that does not forget in time 30 %.  Packed
 // sequences: long enough on average that most chains are full ones.
 // A model per sequence (nx = 4, ny = 2, CV models): the head and the tail of a
 // sequence cost as much as about 1500 of its other steps, and a bundle with a
-// model that settles too late goes back to the scan after 35 us, so from well
-// behind the break-even on:
-//   64 sequences, 533 k steps                       301, 254        208, 239
-//                 the filter alone                  158, 108        115, 107
-//   300,          628 k                             313, 361        216, 369
-//   300,          2.46 M                            769, 415        463, 349
-//                 the filter alone                  359, 162        246, 134
-//   1024,         2.05 M                            561, 514        391, 455
-//   1024,         8.30 M                            2047, 871       1249, 568
+// model that settles too late goes back to the scan after 18 to 31 us:
+//   64 sequences, 890 k steps (on the line)         324, 333        211 (the scan)
+//                 the filter alone                  170, 133        114, 130 (below its line)
+//   300,          2.46 M                            762, 469        445, 390
+//                 the filter alone                  358, 180        244, 154
+//   1024,         3.17 M                            968, 534        577, 414
+//   1024,         8.29 M                            2039, 834       1224, 549
 bool applies(int nx, int ny, int32_t B, int64_t total, bool mixed, bool tv, bool smooth) {
     if (nx < 3 || nx > 4 || ny > 4) return false;
     if (tv) return total >= (mixed ? 1 << 19 : 1 << 18) && total / B >= 512;
-    return total - 1536 * (int64_t)B >= (int64_t)(mixed ? 2 : 1) * (smooth ? 3 << 18 : 3 << 17);
+    return total - 1536 * (int64_t)B >= (int64_t)(mixed ? 2 : 1) * (smooth ? 3 << 18 : 1 << 19);
 }
 
 bool layout(Args& a, char* base, size_t bytes, bool tv) {

@@ -486,9 +486,12 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_down(HmmArgs a, const doubl
 // a step's dependent chain (the broadcasts and KV^2 / 64 FP64 FMAs a lane of the
 // product, two row joins, the scaling), 0.3 us a step at K = 64.  What does not
 // depend on the vector (scaled likelihoods, reciprocal predictions) is formed once
-// for all steps beforehand, in the memory of the results.  Sticky chains (stay
-// 0.9) of 2 to 64 states agree to 1e-14 after 200 to 430 steps.  Filter +
-// smoother at K = 64, T = 65536: 411 us, by the block-element scan 2460 us.
+// for all steps beforehand, in the memory of the results.  kWarm: of chains of 3
+// to 64 states that stay 2 to 50 steps in a state, seen through Gaussian noise, every
+// block has met its predecessor after 128 (stay 0.5) to 384 steps (0.9, 64 states);
+// entries of two runs that have met stay within 2^-47.7 of each other (1400 places),
+// kSame is three times that.  Filter + smoother at K = 64, T = 65536: 396 us, by the
+// block-element scan 2420 us.
 // ---------------------------------------------------------------------------
 constexpr int kWarm = 448, kRepairs = 3, kAhead = 4;
 // Chains that do not forget (permutations, states that stay for hundreds of steps
@@ -1228,11 +1231,10 @@ constexpr int64_t kOverSteps = 32, kOverBlocks = 1024;
 
 // Where overlapped blocks win.  Their time hardly grows with T (the warm-up's
 // kWarm steps are most of it); the scan's does, with T KP^3.  Filter + smoother,
-// us, scan and overlapped: KP = 16: 217 and 242 at T = 2^15, 307 and 266 at
-// 2^16; KP = 32: 301 and 270 at 2^14, 420 and 321 at 2^15; KP = 48: 384 and 331
-// at 2^12, 477 and 340 at 2^13; KP = 64: 395 and 325 at 2^11, 460 and 331 at 2^12.
-// From twice the length where they are even on, as an attempt that fails is
-// time lost (about half of the overlapped time: the smoother's is not made then).
+// us, scan, overlapped, and the scan behind an attempt that is given up: KP = 16, T =
+// 2^16: 294, 246, 353; KP = 32, 2^15: 417, 302, 520; KP = 48, 2^13: 475, 329, 536; KP =
+// 64, 2^12: 458, 322, 518.  At half these lengths (a quarter of them for KP > 32) the
+// two are even: from twice as long on, as a failed attempt is time lost.
 int64_t over_min(int KP) { return KP == 16 ? 1 << 16 : KP == 32 ? 1 << 15 : KP == 48 ? 1 << 13 : 1 << 12; }
 
 }  // namespace

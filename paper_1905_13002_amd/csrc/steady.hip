@@ -945,15 +945,22 @@ hipError_t run_kx(const Args& a, hipStream_t s) {
 }  // namespace
 
 // Sizes alone decide.  The setup is a chain of latencies (nx = 4: 55 us, nx = 16:
-// 100 us) whatever the length, the general scan's arithmetic grows with T nx^3:
-//   nx = 4: FP64  T = 98304 105 us general, 104 here; 2^17 114, 105; 2^18 135, 119
-//           mixed T = 196608 103, 112; 2^18 114, 116; 393216 146, 126 (its general
-//           kernels multiply in FP32): a size between its line and 2^18 gives up 9 us
-//   nx = 3: FP64  T = 196608 104, 96; 2^18 129, 102
-//           mixed T = 393216 115, 114; 2^19 143, 124
+// 100 us) whatever the length, the general scan's arithmetic grows with T nx^3.
+// Filter + smoother, us, general and here, of models that settle in 256 steps (CV at
+// 10 Hz), nx = 3: constant acceleration, 512:
+//   nx = 4: FP64  T = 98304 115, 106; 2^17 120, 107; 2^18 141, 117; 2^20 243, 181
+//           mixed T = 196608 111, 110; 2^18 122, 114; 393216 155, 124; 2^20 191, 162 (its
+//           general kernels multiply in FP32)
+//   nx = 3: FP64  T = 233017 124, 121; 2^18 134, 122; 2^20 368, 180
+//           mixed T = 466101 140, 142; 2^19 147, 148; 2^20 274, 181
 //   nx <= 2: 123 general, 153 here at T = 2^20
-//   nx = 6: T = 20011 354 / 166; nx = 16: T = 10000 553 / 250
-// and the mean length of packed sequences has to hold a head and a tail.
+//   nx = 6: T = 8192 268, 145; nx = 16: 319, 242; nx = 24: 3163, 498; nx = 64: 59867, 1778
+// A model that does not settle in the tables' steps costs the doubling and the idle
+// launches on top: 17 to 23 us at nx <= 4, 25 at nx = 6, 55 to 60 at nx = 16 (70 the
+// filter alone), 130 at nx = 24, 500 at nx = 64.
+// Packed sequences: the tables hold a quarter of the mean length at most.  At a mean of
+// 1024 that is 256 steps; at 512, 128 steps serve only the faster models (64 sequences
+// of nx = 16, settling in 128: 563 general, 243 here; of one that does not, 8 % lost).
 constexpr int64_t kMinSteps = 8192, kMinMean = 1024;
 constexpr int64_t kMinWorkF64 = 6 << 20, kMinWorkF32 = 12 << 20;     // T nx^3, nx <= 4
 
