@@ -30,9 +30,6 @@ constexpr double kSame = 0x1p-98, kRounding = 0x1p-88;
 // Means of settled models, 16 steps a product, have met at 2^-47.5; what they have not
 // forgotten is below 2^-52 of where they started by the setup's count of steps
 constexpr double kSameSettled = 0x1p-94;
-// The attempt ends where a first difference is 2^8 above `near`: such a chain does not
-// come down to kSame in the second pass either
-constexpr double kHopeless = 0x1p16;
 constexpr double kTiny = 8.673617379884035e-19;       // 2^-60
 constexpr double kMeet = 1e-11;      // how far a head's last covariance, formed step by step, may be from the doubled one
 constexpr int kMaxLog = 9;           // settled after at most 2^kMaxLog steps
@@ -297,12 +294,7 @@ __device__ __forceinline__ void store_state(double* p, int64_t c, const Lane& t,
 __device__ __forceinline__ bool again(const Args& a, const Chain& x, double P, double m, double P2, double m2, double met,
                                       double near, bool edge, const Lane& t) {
     const bool same = agree(P, m, P2, m2, met, t), close = agree(P, m, P2, m2, near, t);
-    const bool hopeless = x.live && !edge && !agree(P, m, P2, m2, near * kHopeless, t);
     if (x.live && t.i == 0 && t.j == 0) a.forgets[x.c] = close;
-    if (__any(hopeless)) {
-        if (hopeless) a.ctl[0] = 0;
-        return false;
-    }
     if (x.live && (same || edge)) {
         load_state(a.end[0], x.c, t, P, m);
         store_state(a.end[1], x.c, t, P, m);

@@ -829,11 +829,6 @@ __global__ __launch_bounds__(64) void k_hmm_filter_over(OverArgs o, int pass) {
             out[b * KV + x] = own;
             return;
         }
-        // ten bits in kWarm steps: the others will not come in the repairs'
-        if (pass == 1 && o.l < kWarm && all_sum(fabs(was - al)) * (KV / 64.0) > 1e-3) {
-            if (lane == 0) atomicAdd(o.ctl + 2, 1);
-            return;
-        }
         o.entry[b * KV + x] = al;
     }
     MatVec<KV, false> mv;
@@ -1025,13 +1020,8 @@ __global__ __launch_bounds__(64) void k_hmm_smoother_over(OverArgs o, int pass) 
     } else {
         const double own = in[b * KV + x];
         g = b + 1 < o.nblk ? in[(b + 1) * KV + x] : 0.0;
-        const double was = o.entry[b * KV + x];
-        if (b + 1 == o.nblk || same_dist(was, g, live)) {
+        if (b + 1 == o.nblk || same_dist(o.entry[b * KV + x], g, live)) {
             out[b * KV + x] = own;
-            return;
-        }
-        if (pass == 1 && o.l < kWarm && all_sum(fabs(was - g)) * (KV / 64.0) > 1e-3) {
-            if (lane == 0) atomicAdd(o.ctl + 3, 1);
             return;
         }
         o.entry[b * KV + x] = g;

@@ -367,3 +367,23 @@ def test_priors_far_above_chains(pks, each):
         size = np.sqrt(1.0 + ((means / d) ** 2).sum(-1, keepdims=True))
         assert np.max(np.abs(x[:keep].cpu().numpy() - means) / (d * size)) <= 1e-9
         assert np.max(np.abs(X[:keep].cpu().numpy() - cov) / (d[:, :, None] * d[:, None, :])) <= 1e-9
+
+
+def test_chains_beside_a_gap_in_the_measurements(pks):
+    """Steps without information (R = 1e12 I) over a warm-up's length: the chain that
+    starts behind them is run again from its neighbour's end, and the call stays with
+    the chains."""
+    T, l = 1 << 20, 256
+    rng = np.random.default_rng(23)
+    dts = rng.uniform(0.05, 0.15, size=T)
+    y, _ = wl.simulate_cv_tv(dts, 1.0, 0.25, rng)
+    model = wl.cv_model_tv(dts, 1.0, 0.25)
+    for c in (40, 300, 2000):                     # before chain c's first step, by and large
+        model.R[c * l - 150:c * l + 20] = 1e12 * np.eye(2)
+    ws = pks.workspace(4, 2, T, 1, "fp64", time_varying=True)
+    out = pks.filter_smooth(pks.to_device(model, time_varying=True), torch.as_tensor(y).cuda(), "fp64", ws=ws)
+    torch.cuda.synchronize()
+    assert int(ws[:256].cpu().numpy().view(np.int32)[CTL]) == 1
+    ref = oracle.kf_rts_tv(model.F, model.Q, model.H, model.R, model.m0, model.P0, y)
+    for k, v in zip(("m", "P", "ms", "Ps"), out):
+        assert wl.max_rel_err(v.cpu().numpy(), ref[k]) <= TOL["fp64"], k
