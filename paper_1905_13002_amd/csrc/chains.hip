@@ -1267,16 +1267,16 @@ hipError_t run_nx(const Args& a, bool tv, hipStream_t s) {
 
 // Time-varying models.  Filter + smoother, general scan and chains, us:
 //                                                   FP64            mixed (FP32 elements)
-//   nx = 4, ny = 2, CV, q / r = 4, 2^18 steps       366, 274        273, 259 (an earlier form of the chains)
+//   nx = 4, ny = 2, CV, q / r = 4, 2^18 steps       366, 274        261, 285
 //                   2^19                            686, 337        534, 333
 //                   2^20                            1277, 480       1043, 456
-//   nx = 4, ny = 2, a mixture of models, 2^18       375, 302
+//   nx = 4, ny = 2, a mixture of models, 2^18       375, 302        268, 310
 //                   2^19                            684, 389        535, 390
-//   nx = 3, ny = 1, 2^18                            258, 262        192, 241 (as above)
+//   nx = 3, ny = 1, 2^18                            258, 262        185, 265
 //                   2^19                            540, 310        394, 315
-//   nx = 4, ny = 4, 2^18                            462, 417        360, 369 (as above)
+//   nx = 4, ny = 4, 2^18                            462, 417        354, 420
 //                   2^19                            869, 536        669, 543
-//   nx = 2, ny = 1, 2^20                            551, 934        465, 860 (as above)
+//   nx = 2, ny = 1, 2^20                            551, 934        465, 860 (an earlier form of the chains)
 // (the chains' time hardly depends on nx, the general scan's does).  A model that the
 // pilots give up costs 23 us more than the general scan alone, one that they let by
 // and that does not forget in time 30 %.  Packed
